@@ -1,0 +1,15 @@
+// Many-row GEMM instantiations: 96-row chunks (2 x 4 waves of 3 row tiles).
+#include "gemm_mr.h"
+
+namespace jf {
+
+hipError_t launch_mr_rt6(const void* X, size_t xplane, const void* Wp, const MrPlan& m, const Epi& ep, hipStream_t st) {
+  switch (m.CT) {
+    case 4: return launch_mr_cfg<3, 1, 2, 4, 150>(X, xplane, Wp, m, ep, st);
+    case 8: return launch_mr_cfg<3, 2, 2, 4, 150>(X, xplane, Wp, m, ep, st);
+    case 12: return launch_mr_cfg<3, 3, 2, 4, 150>(X, xplane, Wp, m, ep, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace jf

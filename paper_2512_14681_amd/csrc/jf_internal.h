@@ -102,31 +102,32 @@ hipError_t launch_gemm(int dtype, const void* X, size_t xplane, const void* Wp,
                        const GemmShape& s, const Epi& ep, hipStream_t stream);
 size_t gemm_blocks(const GemmShape& s);
 
-// Column-slice GEMM (gemm_mr.hip), bf16: 8-wave workgroups, each wave all
-// row tiles of a chunk x its own column tiles, over LDS-staged activations
-// (requested once per compute unit); split K writes partials that a second
-// kernel reduces.
+// Many-row GEMM (gemm_mr.h), bf16: 8-wave workgroups over a chunk of rows
+// and a group of columns, both operands staged in LDS; split K writes
+// partials that a second kernel reduces.
 struct MrPlan {
   int R;            // rows
-  int RT;           // row tiles per chunk (2, 4, 6, 8): 16 RT rows per chunk
-  int B;            // column tiles per wave at most
+  int RT;           // row tiles per chunk: 16 RT rows
+  int CT;           // column tiles of a workgroup at most
   int KC;           // 128-wide K-blocks
   int P;            // pack group of the weight matrix
   int T;            // 16-column tiles of N
   int gr;           // column tiles per unit (2: SwiGLU pairs)
-  int n_cg;         // column groups (workgroups along N)
-  int passes;       // column passes per group
+  int n_cg;         // column groups
   int S;            // K splits (partials in Epi::kpart, S x R x N floats)
-  int chunks;       // row chunks of 16 RT rows
+  int chunks;       // row chunks
 };
 // false if the shape is not for this kernel; max_splits 1: no split-K
 // scratch
 bool gemm_mr_plan(MrPlan& m, int R, int N, int K, int epi_kind, int n_cus, int max_splits);
-size_t gemm_mr_lds_bytes(const MrPlan& m);
 // per-block argmax slots (EPI_ARGMAX) the plan's epilogue writes
 int gemm_mr_part_blocks(const MrPlan& m);
 hipError_t launch_gemm_mr(const void* X, size_t xplane, const void* Wp, const MrPlan& m, const Epi& ep,
                           hipStream_t stream);
+// the main kernel of one row-tile count (gemm_mr_rt*.hip)
+typedef hipError_t MrLaunch(const void* X, size_t xplane, const void* Wp, const MrPlan& m, const Epi& ep,
+                            hipStream_t stream);
+MrLaunch launch_mr_rt2, launch_mr_rt4, launch_mr_rt6, launch_mr_rt8, launch_mr_rt10, launch_mr_rt12, launch_mr_rt16;
 
 // Packs W[rows][cols] (row-major) into the kernels' block layout, reading
 // source row rowmap[i] (or i if rowmap is null) from one of up to 4 source

@@ -133,6 +133,22 @@ def test_lm_head_column_slice_chunks(R):
     assert ((g == np.argmax(z, axis=1)) | (top2(z) < 1e-3)).all()
 
 
+@pytest.mark.parametrize("R", [33, 49, 65, 97, 129, 161, 193, 257, 321, 449])
+def test_lm_head_many_rows_ragged(R):
+    """One row past each row-tile count of the many-row GEMM (so the last row
+    tile holds one row, and the last chunk of several may be nearly empty),
+    and an odd number of column tiles (513: uneven column groups, the last
+    tile alone in its packed group).  fp32 sums of 2048 products of order
+    0.02: 1e-3 as above."""
+    d, V = 2048, 8208
+    x = jf_inputs.normal(6, 1, R * d, dtype="bf16").reshape(R, d)
+    w = jf_inputs.normal(6, 2, V * d, std=0.02, dtype="bf16").reshape(V, d)
+    z = bf16_bits_to_float(x) @ bf16_bits_to_float(w).T
+    g, _, logits = run_lm_head(x, w, R, d, V, "bf16")
+    assert np.abs(logits - z).max() < 1e-3
+    assert ((g == np.argmax(z, axis=1)) | (top2(z) < 1e-3)).all()
+
+
 def test_lm_head_full_size_config3():
     """LM head of the 7B shape: hidden [64, 3584] ~ N(0,1), W [152064, 3584] ~
     N(0, 0.02), bf16; per-row argmax and the perturbed-draft acceptance."""
