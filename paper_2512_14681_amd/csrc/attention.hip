@@ -615,7 +615,10 @@ __global__ void __launch_bounds__(512, 1) k_attn_lds(AttnArgs a) {
 constexpr long kAttnQt2Work = 50000;
 
 // The LDS-shared form: query groups of up to 8 tiles (balanced), and key
-// splits of at least 3 pages up to about 256 blocks in all.  Splits of one
+// splits of at least 3 pages up to 256 blocks in all: one block runs on a
+// compute unit at a time, so a few blocks more than that cost a second round
+// (264 -> 252 blocks at P = 8000 / n = 48: 41.9 -> 37.5 us with the merge;
+// 264 -> 220 at P = 2048 / n = 192: 42.0 -> 32.3 us).  Splits of one
 // or two pages cost more in partials and their merge than the extra blocks
 // gain inside a step (1024-token prefix: 64 rows 5182 -> 5066 us, 128 rows
 // 7171 -> 6943 us; 192 and 256 rows unchanged; the attention workload at
@@ -625,7 +628,7 @@ static void attn_lds_plan(AttnArgs& a) {
   const int groups = (ntiles + 7) / 8;
   a.qg = (ntiles + groups - 1) / groups;
   const int pages = (a.keys_ub + kPage - 1) / kPage;
-  int s = (256 + a.G * groups - 1) / (a.G * groups);
+  int s = std::max(1, 256 / (a.G * groups));
   s = std::min(s, (pages + 2) / 3);
   const int min_s = (pages + kAttnMaxPages - 3) / (kAttnMaxPages - 2);
   a.splits = std::max(1, std::min(kAttnMaxSplits, std::max(s, min_s)));
