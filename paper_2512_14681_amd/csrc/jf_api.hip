@@ -429,12 +429,6 @@ static jf_status forward(jf_model* m, const int32_t* d_tokens, int R, const SegA
   void* xn = m->ws + L.w_xn;
   int32_t* pos = m->at<int32_t>(L.w_pos);
 
-  if (pk)
-    HIP_TRY(launch_tree_packed(pk->n_blocks, pk->n, pk->mask, state, m->flags(), m->at<int32_t>(L.w_parent),
-                               pos, m->at<uint64_t>(L.w_vis), st));
-  else
-    HIP_TRY(launch_tree(sg, R, state, m->flags(), m->at<int32_t>(L.w_parent), pos,
-                        m->at<uint64_t>(L.w_vis), st));
   const size_t Rp = L.Rp;
   const size_t pl_d = Rp * d, pl_h = Rp * Hhd, pl_f = Rp * F;  // activation plane strides
   // The RMSNorms are folded into the projections.  Every residual add writes
@@ -452,8 +446,10 @@ static jf_status forward(jf_model* m, const int32_t* d_tokens, int R, const SegA
     ep.gain_next = gain; ep.xg = xn; ep.xg_plane = pl_d; ep.ss_out = ss; ep.ss_clear = clear;
     ep.ss_stride = ss_stride;
   };
-  HIP_TRY(launch_embed(dt, d_tokens, R, m->packed + L.p_embed, (const float*)(m->layer(0) + L.l_an), d,
-                       c.vocab, h, xn, pl_d, ss_a, ss_f, ss_stride, m->flags(), st));
+  const ForestOut fo{state, m->flags(), m->at<int32_t>(L.w_parent), pos, m->at<uint64_t>(L.w_vis)};
+  HIP_TRY(launch_tree_embed(dt, pk ? nullptr : &sg, pk ? pk->n_blocks : 0, pk ? pk->n : 0, pk ? pk->mask : 0, R, fo,
+                            d_tokens, m->packed + L.p_embed, (const float*)(m->layer(0) + L.l_an), d, c.vocab, h, xn,
+                            pl_d, ss_a, ss_f, ss_stride, st));
   const int keys_ub = std::min(m->C_ub + R, c.max_ctx);
   // The attention half of every layer as one persistent launch (layer.hip)
   // when the step qualifies; its plan is the same for all layers.

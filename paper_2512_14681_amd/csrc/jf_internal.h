@@ -140,21 +140,26 @@ struct SegArgs {
   int32_t n;
   int32_t first[16], nrows[16], attach[16], role[16], verify_from[16];
 };
-hipError_t launch_tree(const SegArgs& segs, int R, const int32_t* state, int32_t* flags,
-                       int32_t* parent, int32_t* pos, uint64_t* vis, hipStream_t stream);
-// the packed noisy/clean layout of a training sequence; mask as JF_MASK_* of jf.h
+// where a step's forest goes (rows as in k_tree_embed), and its flags
+struct ForestOut {
+  const int32_t* state;   // state[0] = committed length C
+  int32_t* flags;
+  int32_t* parent;
+  int32_t* pos;
+  uint64_t* vis;
+};
 constexpr int kMaskNoisyContext = 0, kMaskCleanContext = 1;
-hipError_t launch_tree_packed(int n_blocks, int n, int mask, const int32_t* state, int32_t* flags,
-                              int32_t* parent, int32_t* pos, uint64_t* vis, hipStream_t stream);
 
-// Embedding rows h[r] = E[token r] (fp32, row-major [R][d]) with the first
+// The step's forest, from segs or (segs null) from the packed noisy/clean
+// layout of n_blocks blocks of n rows (mask as JF_MASK_* of jf.h), and the
+// embedding rows h[r] = E[token r] (fp32, row-major [R][d]) with the first
 // RMSNorm's input: activation planes of h * gamma in the GEMM-input layout
 // (xg) and each row's sum of squares stored into the fixed-point accumulator
 // ss (three word planes of ss_stride entries); ss_clear is zeroed.
-hipError_t launch_embed(int dtype, const int32_t* tokens, int R, const void* embed,
-                        const float* gamma, int d, int V, float* h, void* xg, size_t xplane,
-                        uint64_t* ss, uint64_t* ss_clear, int ss_stride, int32_t* flags,
-                        hipStream_t stream);
+hipError_t launch_tree_embed(int dtype, const SegArgs* segs, int n_blocks, int n, int mask, int R, const ForestOut& f,
+                             const int32_t* tokens, const void* embed, const float* gamma, int d, int V, float* h,
+                             void* xg, size_t xplane, uint64_t* ss, uint64_t* ss_clear, int ss_stride,
+                             hipStream_t stream);
 
 constexpr int kAttnMaxSplits = 32;
 

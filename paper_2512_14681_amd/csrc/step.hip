@@ -4,6 +4,7 @@
 // residual adds write h * gain and the row sums of squares, the consumer
 // GEMMs scale their output rows by 1 / rms.)
 #include "jf_device.h"
+#include "jf_epilogue.h"
 #include "jf_internal.h"
 
 namespace jf {
@@ -11,49 +12,63 @@ namespace jf {
 // ---- a1: rows of the step as a forest (Sec. 3.2, input assembly of App. A Alg. 1) ----
 // parent[r]: row whose argmax r is checked against (-1: a root, predicted by
 // the last committed row); pos[r] = C + depth(r); vis[r]: bit j set iff row j
-// is r or an ancestor of r.  One thread per row walks its own ancestor chain
-// (after par[] holds every row's parent).
-__device__ void tree_walk(const int32_t* par, int r, int R, const int32_t* state, int32_t* parent,
-                          int32_t* pos, uint64_t* vis) {
-  if (r >= R) return;
-  uint64_t w[kVisWords] = {};
-  int depth = 0;
-  int x = r;
-  w[x >> 6] |= 1ull << (x & 63);
-  while (par[x] >= 0) {
-    x = par[x];
-    w[x >> 6] |= 1ull << (x & 63);
-    ++depth;
-  }
-  parent[r] = par[r];
-  pos[r] = state[0] + depth;
-  for (int i = 0; i < kVisWords; ++i) vis[r * kVisWords + i] = w[i];
-}
+// is r or an ancestor of r.
+//
+// One block, a row per thread.  A row's ancestors are runs of consecutive
+// rows: its own run (head .. r), then the ancestors of the row its run hangs
+// under.  Each row starts from its run and, in steps that double the number
+// of runs it covers, takes over the mask and depth of the row it has reached;
+// a linear draft or a prompt chunk (one run) needs none of them, a
+// multi-block forest two or three.  Walking the ancestors row by row instead
+// cost 10 / 18 / 70 us at 64 / 192 / 512 rows.
+struct ForestShared {
+  uint64_t w[kMaxRows][kVisWords + 1];  // padded: rows in different banks
+  int32_t anc[kMaxRows], dep[kMaxRows];
+};
 
-__global__ void __launch_bounds__(kMaxRows) k_tree(SegArgs sg, int R, const int32_t* state, int32_t* flags,
-                                                   int32_t* parent, int32_t* pos, uint64_t* vis) {
-  __shared__ int32_t par[kMaxRows];
-  const int r = threadIdx.x;
-  if (r == 0 && flags) *flags = 0;  // flags are per step
-  if (r < R) {
-    int p = -1;
-    for (int s = 0; s < sg.n; ++s) {
-      if (r >= sg.first[s] && r < sg.first[s] + sg.nrows[s]) {
-        p = (r == sg.first[s]) ? sg.attach[s] : r - 1;
-        break;
-      }
+// Thread r: row r (< R) of a run that starts at row head and hangs under row
+// attach (-1: none).
+__device__ void build_forest(int r, int R, int head, int attach, int C, int32_t* parent, int32_t* pos, uint64_t* vis,
+                             ForestShared& sh) {
+  uint64_t w[kVisWords];
+#pragma unroll
+  for (int i = 0; i < kVisWords; ++i) {  // bits head .. r
+    const int lo = max(head - 64 * i, 0), hi = min(r - 64 * i, 63);
+    w[i] = lo <= hi && lo < 64 ? ((2ull << hi) - 1ull) & ~((1ull << lo) - 1ull) : 0ull;
+  }
+  int anc = attach, dep = r - head;
+  while (__syncthreads_or(r < R && anc >= 0)) {
+    if (r < R) {
+#pragma unroll
+      for (int i = 0; i < kVisWords; ++i) sh.w[r][i] = w[i];
+      sh.anc[r] = anc;
+      sh.dep[r] = dep;
     }
-    par[r] = p;
+    __syncthreads();
+    if (r < R && anc >= 0) {
+#pragma unroll
+      for (int i = 0; i < kVisWords; ++i) w[i] |= sh.w[anc][i];
+      dep += sh.dep[anc] + 1;
+      anc = sh.anc[anc];
+    }
   }
-  __syncthreads();
-  tree_walk(par, r, R, state, parent, pos, vis);
+  if (r < R) {
+    parent[r] = r > head ? r - 1 : attach;
+    pos[r] = C + dep;
+#pragma unroll
+    for (int i = 0; i < kVisWords; ++i) vis[(size_t)r * kVisWords + i] = w[i];
+  }
 }
 
-hipError_t launch_tree(const SegArgs& segs, int R, const int32_t* state, int32_t* flags,
-                       int32_t* parent, int32_t* pos, uint64_t* vis, hipStream_t st) {
-  if (R < 1 || R > kMaxRows) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_tree, dim3(1), dim3(kMaxRows), 0, st, segs, R, state, flags, parent, pos, vis);
-  return hipGetLastError();
+// The run of row r in a step's segments.
+__device__ __forceinline__ void segment_run(const SegArgs& sg, int r, int& head, int& attach) {
+  head = 0;
+  attach = -1;
+  for (int s = 0; s < sg.n; ++s)
+    if (r >= sg.first[s] && r < sg.first[s] + sg.nrows[s]) {
+      head = sg.first[s];
+      attach = sg.attach[s];
+    }
 }
 
 // Packed training sequence (Sec. 3.1 noise-aware causal attention, App. C
@@ -64,33 +79,12 @@ hipError_t launch_tree(const SegArgs& segs, int R, const int32_t* state, int32_t
 // (noisy-context mask) or of clean block i - 1 (clean-context mask).  Both
 // copies of block i get depths i n .. i n + n - 1, the block's own
 // positions.
-__global__ void __launch_bounds__(kMaxRows) k_tree_packed(int n_blocks, int n, int mask, const int32_t* state,
-                                                          int32_t* flags, int32_t* parent, int32_t* pos,
-                                                          uint64_t* vis) {
-  __shared__ int32_t par[kMaxRows];
-  const int R = 2 * n_blocks * n;
-  const int r = threadIdx.x;
-  if (r == 0 && flags) *flags = 0;
-  if (r < R) {
-    const int b = r / (2 * n), within = r - b * 2 * n;
-    const int copy = within / n, k = within - copy * n;   // copy 0: noisy, 1: clean
-    int p;
-    if (k > 0) p = r - 1;
-    else if (b == 0) p = -1;
-    else if (copy == 1 || mask == kMaskCleanContext) p = 2 * b * n - 1;      // last row of clean b - 1
-    else p = (2 * b - 1) * n - 1;                                            // last row of noisy b - 1
-    par[r] = p;
-  }
-  __syncthreads();
-  tree_walk(par, r, R, state, parent, pos, vis);
-}
-
-hipError_t launch_tree_packed(int n_blocks, int n, int mask, const int32_t* state, int32_t* flags,
-                              int32_t* parent, int32_t* pos, uint64_t* vis, hipStream_t st) {
-  if (n_blocks < 1 || n < 1 || 2 * n_blocks * n > kMaxRows) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_tree_packed, dim3(1), dim3(kMaxRows), 0, st, n_blocks, n, mask, state, flags, parent,
-                     pos, vis);
-  return hipGetLastError();
+__device__ __forceinline__ void packed_run(int n, int mask, int r, int& head, int& attach) {
+  const int b = r / (2 * n), copy = (r - b * 2 * n) / n;  // copy 0: noisy, 1: clean
+  head = (2 * b + copy) * n;
+  if (b == 0) attach = -1;
+  else if (copy == 1 || mask == kMaskCleanContext) attach = 2 * b * n - 1;  // last row of clean b - 1
+  else attach = (2 * b - 1) * n - 1;                                        // last row of noisy b - 1
 }
 
 // ---- block reduction helper --------------------------------------------------
@@ -105,47 +99,67 @@ __device__ __forceinline__ float block_sum(float v, float* sh) {
   return t;
 }
 
-// ---- a2: embedding rows + the first RMSNorm's input -------------------------------
-// h = E[token] (fp32); xg = h * gamma as activation planes in the GEMM-input
-// layout; the row's sum of squares goes to the fixed-point accumulator ss
-// (the QKV projection applies 1 / rms to its output rows).  Block 0 also
-// zeroes ss_clear, the accumulator the first residual add fills.
-template <typename T>
-__global__ void __launch_bounds__(256)
-    k_embed(const int32_t* __restrict__ tokens, const T* __restrict__ E, const float* __restrict__ gamma, int d,
-            int V, float* __restrict__ h, T* __restrict__ xg, size_t xplane, uint64_t* ss, uint64_t* ss_clear,
-            int ss_stride, int32_t* flags) {
-  __shared__ float sh[16];
-  const int r = blockIdx.x;
-  if (r == 0 && ss_clear)
-    for (int i = threadIdx.x; i < 3 * ss_stride; i += blockDim.x)
-      __hip_atomic_store(ss_clear + i, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  int tok = tokens[r];
-  if (tok < 0 || tok >= V) {
-    if (threadIdx.x == 0 && flags) atomicOr(flags, 1);
-    tok = 0;
-  }
-  const T* e = E + (size_t)tok * d;
-  // d <= 4096: every thread's (at most 16) elements and gains are loaded at
-  // once, then stored.
-  float v[16], gm[16];
+// ---- a1 + a2: the forest, the embedding rows and the first RMSNorm's input --------
+// Block 0 builds the forest and the step's flags (bit 0: a token outside the
+// vocabulary); block r + 1 gathers row r: h = E[token] (fp32); xg = h * gamma
+// as activation planes in the GEMM-input layout; the row's sum of squares
+// goes to the fixed-point accumulator ss (the QKV projection applies 1 / rms
+// to its output rows).  Block 1 also zeroes ss_clear, the accumulator the
+// first residual add fills.  The two share a launch because neither reads
+// the other's results and each is little more than its latency: separate
+// launches took 3 us more on every step.  A thread takes 8 adjacent columns
+// (d <= 4096), which the layout keeps together: 16-byte loads and stores
+// (2-byte ones: 12.7 us at 64 rows).
+constexpr int kEmbedThreads = 512;
+
+template <typename T> __device__ __forceinline__ void load8_f32(const T* p, float (&v)[8]) {
+  const Frag<T> f = frag_load<T>(p);
+  if constexpr (sizeof(T) == 2) {
+    const uint32_t u[4] = {f.v.x, f.v.y, f.v.z, f.v.w};
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int i = threadIdx.x + 256 * k;
-    v[k] = i < d ? to_f32<T>(e[i]) : 0.f;
-    gm[k] = i < d ? gamma[i] : 0.f;
-  }
-  float ss_part = 0.f;
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int i = threadIdx.x + 256 * k;
-    if (i < d) {
-      h[(size_t)r * d + i] = v[k];
-      act_store<T>(xg + act_offset(r, i, d), xplane, v[k] * gm[k]);
+    for (int i = 0; i < 4; ++i) {
+      v[2 * i] = __uint_as_float(u[i] << 16);
+      v[2 * i + 1] = __uint_as_float(u[i] & 0xFFFF0000u);
     }
-    ss_part += v[k] * v[k];
+  } else {
+    v[0] = f.lo.x; v[1] = f.lo.y; v[2] = f.lo.z; v[3] = f.lo.w;
+    v[4] = f.hi.x; v[5] = f.hi.y; v[6] = f.hi.z; v[7] = f.hi.w;
   }
-  const float tot = block_sum(ss_part, sh);
+}
+
+template <typename T>
+__device__ void embed_row(int r, const int32_t* tokens, const T* __restrict__ E, const float* __restrict__ gamma, int d,
+                          int V, float* __restrict__ h, T* __restrict__ xg, size_t xplane, uint64_t* ss,
+                          uint64_t* ss_clear, int ss_stride, float* sh) {
+  if (r == 0 && ss_clear)
+    for (int i = threadIdx.x; i < 3 * ss_stride; i += kEmbedThreads)
+      __hip_atomic_store(ss_clear + i, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int c = 8 * threadIdx.x;
+  float gm[8] = {}, v[8] = {};
+  if (c < d) load8_f32<float>(gamma + c, gm);
+  int tok = tokens[r];
+  if (tok < 0 || tok >= V) tok = 0;
+  if (c < d) load8_f32<T>(E + (size_t)tok * d + c, v);
+  float part = 0.f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    part += v[k] * v[k];
+    gm[k] *= v[k];
+  }
+  if (c < d) {
+    float4* hp = reinterpret_cast<float4*>(h + (size_t)r * d + c);
+    hp[0] = make_float4(v[0], v[1], v[2], v[3]);
+    hp[1] = make_float4(v[4], v[5], v[6], v[7]);
+    T* x = xg + act_offset(r, c, d);
+    if constexpr (sizeof(T) == 2) {
+      act_store8(x, xplane, gm);
+    } else {
+      float4* xp = reinterpret_cast<float4*>(x);
+      xp[0] = make_float4(gm[0], gm[1], gm[2], gm[3]);
+      xp[1] = make_float4(gm[4], gm[5], gm[6], gm[7]);
+    }
+  }
+  const float tot = block_sum(part, sh);
   if (threadIdx.x == 0) {
     uint64_t w[3];
     ss_split(tot, w);
@@ -154,17 +168,66 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-hipError_t launch_embed(int dtype, const int32_t* tokens, int R, const void* embed,
-                        const float* gamma, int d, int V, float* h, void* xg, size_t xplane,
-                        uint64_t* ss, uint64_t* ss_clear, int ss_stride, int32_t* flags,
-                        hipStream_t st) {
-  if (R < 1 || R > ss_stride || d > 16 * 256) return hipErrorInvalidValue;
-  if (dtype == 1)
-    hipLaunchKernelGGL(k_embed<bf16_t>, dim3(R), dim3(256), 0, st, tokens, (const bf16_t*)embed, gamma,
-                       d, V, h, (bf16_t*)xg, xplane, ss, ss_clear, ss_stride, flags);
-  else
-    hipLaunchKernelGGL(k_embed<float>, dim3(R), dim3(256), 0, st, tokens, (const float*)embed, gamma, d,
-                       V, h, (float*)xg, xplane, ss, ss_clear, ss_stride, flags);
+// Block 0 of both kernels.
+__device__ void forest_block(int R, int head, int attach, const int32_t* tokens, int V, const ForestOut& f,
+                             ForestShared& sh) {
+  const int r = threadIdx.x;
+  const int tok = r < R ? tokens[r] : 0;
+  const int bad = __syncthreads_or(tok < 0 || tok >= V);
+  if (r == 0) *f.flags = bad ? 1 : 0;  // flags are per step
+  build_forest(r, R, head, attach, f.state[0], f.parent, f.pos, f.vis, sh);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kEmbedThreads)
+    k_tree_embed(SegArgs sg, int R, ForestOut f, const int32_t* __restrict__ tokens, const T* __restrict__ E,
+                 const float* __restrict__ gamma, int d, int V, float* __restrict__ h, T* __restrict__ xg,
+                 size_t xplane, uint64_t* ss, uint64_t* ss_clear, int ss_stride) {
+  __shared__ ForestShared sh;
+  if (blockIdx.x == 0) {
+    int head, attach;
+    segment_run(sg, threadIdx.x, head, attach);
+    forest_block(R, head, attach, tokens, V, f, sh);
+  } else {
+    embed_row<T>(blockIdx.x - 1, tokens, E, gamma, d, V, h, xg, xplane, ss, ss_clear, ss_stride,
+                 reinterpret_cast<float*>(&sh));
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kEmbedThreads)
+    k_tree_packed_embed(int n, int mask, int R, ForestOut f, const int32_t* __restrict__ tokens,
+                        const T* __restrict__ E, const float* __restrict__ gamma, int d, int V, float* __restrict__ h,
+                        T* __restrict__ xg, size_t xplane, uint64_t* ss, uint64_t* ss_clear, int ss_stride) {
+  __shared__ ForestShared sh;
+  if (blockIdx.x == 0) {
+    int head, attach;
+    packed_run(n, mask, threadIdx.x, head, attach);
+    forest_block(R, head, attach, tokens, V, f, sh);
+  } else {
+    embed_row<T>(blockIdx.x - 1, tokens, E, gamma, d, V, h, xg, xplane, ss, ss_clear, ss_stride,
+                 reinterpret_cast<float*>(&sh));
+  }
+}
+
+hipError_t launch_tree_embed(int dtype, const SegArgs* segs, int n_blocks, int n, int mask, int R, const ForestOut& f,
+                             const int32_t* tokens, const void* embed, const float* gamma, int d, int V, float* h,
+                             void* xg, size_t xplane, uint64_t* ss, uint64_t* ss_clear, int ss_stride,
+                             hipStream_t st) {
+  static_assert(kEmbedThreads >= kMaxRows, "a row per thread");
+  if (R < 1 || R > kMaxRows || R > ss_stride || d > 8 * kEmbedThreads || d % 8) return hipErrorInvalidValue;
+  if (!segs && (n_blocks < 1 || n < 1 || 2 * n_blocks * n != R)) return hipErrorInvalidValue;
+  auto launch = [&](auto tag) {
+    using T = decltype(tag);
+    if (segs)
+      hipLaunchKernelGGL(k_tree_embed<T>, dim3(R + 1), dim3(kEmbedThreads), 0, st, *segs, R, f, tokens,
+                         (const T*)embed, gamma, d, V, h, (T*)xg, xplane, ss, ss_clear, ss_stride);
+    else
+      hipLaunchKernelGGL(k_tree_packed_embed<T>, dim3(R + 1), dim3(kEmbedThreads), 0, st, n, mask, R, f, tokens,
+                         (const T*)embed, gamma, d, V, h, (T*)xg, xplane, ss, ss_clear, ss_stride);
+  };
+  if (dtype == 1) launch(bf16_t{});
+  else launch(float{});
   return hipGetLastError();
 }
 

@@ -65,6 +65,21 @@ def test_packed_tiny(mask, N, n):
     check(z, g, ref, 1e-4)
 
 
+@pytest.mark.parametrize("mask", [opk.NOISY_CONTEXT, opk.CLEAN_CONTEXT])
+@pytest.mark.parametrize("N,n", [(33, 1), (21, 3), (64, 1)])
+def test_packed_long_chains(mask, N, n):
+    """Many short blocks: chains of up to 64 runs of rows, which the forest
+    builder covers in doubling steps (33 and 21 are no powers of two), across
+    mask words."""
+    w = jf_inputs.model_weights(TINY, seed=0)
+    prompt = jf_inputs.prompt(1, 24, TINY["vocab"])
+    noisy = blocks(15, N, n, TINY["vocab"])
+    clean = blocks(16, N, n, TINY["vocab"])
+    g, z, _ = run(TINY, w, prompt, noisy, clean, mask)
+    ref = opk.packed_logits(DecoderOracle(TINY, w), prompt, noisy, clean, mask)
+    check(z, g, ref, 1e-4)
+
+
 def test_packed_mid_bf16():
     """bf16 decoder (d 2048), 4 blocks of 16 (128 rows, four 32-row chunks),
     noise-aware mask."""
