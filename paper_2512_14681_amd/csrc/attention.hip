@@ -74,17 +74,46 @@ __device__ __forceinline__ uint32_t vis_bits8(const uint64_t (&vw)[kVisWords], i
 }
 
 // The visibility words of in-step row r: from vis ([R][kVisWords]), or the
-// causal mask (rows 0..r) when vis is null.
+// causal mask (rows 0..r) when vis is null.  One (uniform) branch around all
+// the loads, so that they are in flight together.
 __device__ __forceinline__ void vis_words(const uint64_t* vis, int r, uint64_t (&vw)[kVisWords]) {
+  if (vis) {
+    const uint64_t* p = vis + (size_t)r * kVisWords;
 #pragma unroll
-  for (int i = 0; i < kVisWords; ++i) {
-    if (vis) {
-      vw[i] = vis[(size_t)r * kVisWords + i];
-    } else {
+    for (int i = 0; i < kVisWords; ++i) vw[i] = p[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < kVisWords; ++i) {
       const int lo = i * 64;
       vw[i] = r < lo ? 0ull : (r - lo >= 63 ? ~0ull : ((2ull << (r - lo)) - 1ull));
     }
   }
+}
+
+// Maximum over the four lanes that share a query column (l, l ^ 16, l ^ 32,
+// l ^ 48), on the vector unit: an exchange through LDS costs its latency
+// twice in the middle of every chunk's dependency chain.
+__device__ __forceinline__ float column_max(float v) {
+  const uint32_t u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const float w = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const uint32_t x = __float_as_uint(w);
+  const auto b = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// Four adjacent columns of a row as activation planes (bf16: one 8-byte store
+// a plane; p is a multiple of 4 elements into the layout's 8-column groups).
+template <typename T> __device__ __forceinline__ void act_store4(T* p, size_t plane, const float (&v)[4]);
+template <> __device__ __forceinline__ void act_store4<bf16_t>(bf16_t* p, size_t plane, const float (&v)[4]) {
+  uint32_t h[2], l[2];
+  split2(v[0], v[1], h[0], l[0]);
+  split2(v[2], v[3], h[1], l[1]);
+  *reinterpret_cast<uint2*>(p) = make_uint2(h[0], h[1]);
+  *reinterpret_cast<uint2*>(p + plane) = make_uint2(l[0], l[1]);
+}
+template <> __device__ __forceinline__ void act_store4<float>(float* p, size_t plane, const float (&v)[4]) {
+  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
 // Low n bits set, n clamped to [0, 8].
@@ -199,22 +228,20 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnArgs a) {
           for (int cc = 0; cc < HD / 32; ++cc) mfma(sc[kt], kf[kt][cc], qf[t][cc]);
         }
       }
-      // visible: below lim, and either in the prefix or marked in the row's mask
-      const uint32_t vis = low_bits8(lim - key0) & (low_bits8(C - key0) | vis_bits8(vw[t], key0 - C));
       float p[8];
-      float mx = -INFINITY;
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+      for (int e = 0; e < 8; ++e) p[e] = sc[e >> 2][e & 3];
+      // visible: below lim, and either in the prefix or marked in the row's
+      // mask (no branch around it for chunks inside the prefix: the two
+      // chunks' loads would all have to be in registers before it, 164 -> 226
+      // registers and 1.5 us more at 1024 keys)
+      const uint32_t vis = low_bits8(lim - key0) & (low_bits8(C - key0) | vis_bits8(vw[t], key0 - C));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int e = kt * 4 + i;
-          const float v = ((vis >> e) & 1u) ? sc[kt][i] * scale : -INFINITY;
-          p[e] = v;
-          mx = fmaxf(mx, v);
-        }
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float m_new = fmaxf(m_run[t], mx);
+      for (int e = 0; e < 8; ++e) p[e] = ((vis >> e) & 1u) ? p[e] : -INFINITY;
+      float mx = p[0];
+#pragma unroll
+      for (int e = 1; e < 8; ++e) mx = fmaxf(mx, p[e]);
+      const float m_new = fmaxf(m_run[t], column_max(mx) * scale);
       // No branch: the MFMAs need every lane.  A query with nothing visible
       // yet keeps p = 0 and m = -inf.
       const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
@@ -223,7 +250,7 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnArgs a) {
       float psum = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        p[e] = __builtin_amdgcn_exp2f(p[e] - m_use);
+        p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(p[e], scale, -m_use));
         psum += p[e];
       }
       l_run[t] = l_run[t] * alpha + psum;
@@ -327,43 +354,49 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnArgs a) {
   }
 }
 
-// Merges the splits' (max, sum, O) states of 16 query rows x 32 dims per
-// block in split order; every load of a thread is issued at once (SMAX >= S
-// splits unrolled, the extra ones re-reading split S - 1 with weight 0).
+// Merges the splits' (max, sum, O) states of 16 query rows x (up to) 64 dims
+// per block in split order, four dims a thread; every load of a thread is
+// issued at once (SMAX >= S splits unrolled, the extra ones re-reading split
+// S - 1 with weight 0).
+constexpr int combine_dims(int HD) { return HD < 64 ? HD : 64; }
+
 template <typename T, int HD, int SMAX>
 __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
-  const int g = blockIdx.x, tile = blockIdx.y, d0 = blockIdx.z * 32;
+  constexpr int DB = combine_dims(HD), TQ = DB / 4;  // dims of a block, threads of a query row
+  if (threadIdx.x >= 16 * TQ) return;
+  const int g = blockIdx.x, tile = blockIdx.y;
   const int S = a.splits;
   const int grp = a.H / a.G, R = a.R, nq = grp * R;
   const size_t nrow = (size_t)R * a.H;
+  const int q = threadIdx.x / TQ, dim = blockIdx.z * DB + 4 * (threadIdx.x % TQ);
+  const int qq = min(tile * 16 + q, nq - 1);
+  const int hq = qq / R, rr = qq - hq * R;
+  const size_t qidx = (size_t)rr * a.H + g * grp + hq;
+  float2 ml[SMAX];
+  float4 ov[SMAX];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int e = threadIdx.x + 256 * j;
-    const int q = e >> 5, dim = d0 + (e & 31);
-    const int qq = min(tile * 16 + q, nq - 1);
-    const int hq = qq / R, rr = qq - hq * R;
-    const size_t qidx = (size_t)rr * a.H + g * grp + hq;
-    float m[SMAX], l[SMAX], ov[SMAX];
+  for (int sp = 0; sp < SMAX; ++sp) {
+    const size_t i = (size_t)min(sp, S - 1) * nrow + qidx;
+    ml[sp] = *reinterpret_cast<const float2*>(a.ml_part + i * 2);
+    ov[sp] = *reinterpret_cast<const float4*>(a.o_part + i * HD + dim);
+  }
+  float M = -INFINITY;
 #pragma unroll
-    for (int sp = 0; sp < SMAX; ++sp) {
-      const size_t i = (size_t)min(sp, S - 1) * nrow + qidx;
-      m[sp] = a.ml_part[i * 2];
-      l[sp] = a.ml_part[i * 2 + 1];
-      ov[sp] = a.o_part[i * HD + dim];
-    }
-    float M = -INFINITY;
+  for (int sp = 0; sp < SMAX; ++sp) M = fmaxf(M, ml[sp].x);
+  float num[4] = {0.f, 0.f, 0.f, 0.f}, den = 0.f;
 #pragma unroll
-    for (int sp = 0; sp < SMAX; ++sp) M = fmaxf(M, m[sp]);
-    float num = 0.f, den = 0.f;
+  for (int sp = 0; sp < SMAX; ++sp) {
+    const float w = (sp >= S || ml[sp].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml[sp].x - M);
+    num[0] += ov[sp].x * w;
+    num[1] += ov[sp].y * w;
+    num[2] += ov[sp].z * w;
+    num[3] += ov[sp].w * w;
+    den += ml[sp].y * w;
+  }
+  if (tile * 16 + q < nq) {
 #pragma unroll
-    for (int sp = 0; sp < SMAX; ++sp) {
-      const float w = (sp >= S || m[sp] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m[sp] - M);
-      num += ov[sp] * w;
-      den += l[sp] * w;
-    }
-    if (tile * 16 + q < nq)
-      act_store<T>(reinterpret_cast<T*>(a.out) + act_offset(rr, (g * grp + hq) * HD + dim, a.H * HD), a.out_plane,
-                   num / den);
+    for (int k = 0; k < 4; ++k) num[k] /= den;
+    act_store4<T>(reinterpret_cast<T*>(a.out) + act_offset(rr, (g * grp + hq) * HD + dim, a.H * HD), a.out_plane, num);
   }
 }
 
@@ -374,7 +407,14 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
 // every wave, so the keys are fetched once per query group instead of once
 // per query tile.  Pages stream through a register ring two pages deep into
 // two LDS buffers; the per-wave maths (S^T = K Q^T, online softmax, O^T +=
-// V^T P^T, Q and P as hi + lo bf16 terms) is that of k_attn.  Each wave owns
+// V^T P^T, Q and P as hi + lo bf16 terms) is that of k_attn, over a page at
+// a time: one maximum, one rescale (skipped while no maximum moves) and no
+// mask for pages inside the prefix.  What bounds it is vector work and matrix
+// instructions in turn (a page and wave: 64 matrix instructions, and before
+// this about 400 vector instructions, half of them masks that every prefix
+// key passes): P = 2048, n = 192 32.3 -> 28.1 us, P = 8000, n = 320 117 ->
+// 91 us, P = 8000, n = 48 33.8 -> 28.7 us (with the merge, four dims a thread
+// instead of one).  Each wave owns
 // its query tile's state, so there is no merge across waves; with several
 // splits the states go to the combine kernel.
 //
@@ -482,66 +522,67 @@ __global__ void __launch_bounds__(512, 1) k_attn_lds(AttnArgs a) {
 #pragma unroll
   for (int dt = 0; dt < HD / 16; ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  // one 32-key half h of the page in LDS buffer b (keys kp0 + 32 h ..)
-  auto compute = [&](int b, int kp0, int h) {
+  // The page in LDS buffer b (keys kp0 ..): the four 16-key score tiles, one
+  // softmax step over the 64 keys, then the two 32-key halves of P V.
+  auto compute = [&](int b, int kp0) {
     const uint4* lk = reinterpret_cast<const uint4*>(s_kv + (size_t)b * kAttnLdsPageElems);
     const uint4* lv = lk + 8 * HD;
-    Frag<bf16_t> kf[2][HD / 32], vf[HD / 16];
+    f32x4_t sh[4], sl[4];
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      const int rr = 32 * h + 8 * (ql >> 2) + 4 * kt + (ql & 3);
+    for (int t = 0; t < 4; ++t) sh[t] = sl[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int cc = 0; cc < HD / 32; ++cc) kf[kt][cc].v = lk[16 * rr + ((kg + 4 * cc) ^ kswz(rr))];
-    }
+    for (int cc = 0; cc < HD / 32; ++cc)
 #pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) {
-      const int d = dt * 16 + ql, pc = 4 * h + kg;
-      vf[dt].v = lv[8 * d + (pc ^ ((d >> 1) & 7))];
-    }
-    const int key0 = kp0 + 32 * h + 8 * kg;  // key of p[0]; p[e] is key0 + e
-    f32x4_t sc[2];
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      f32x4_t sh = f32x4_t{0.f, 0.f, 0.f, 0.f}, sl = sh;
-#pragma unroll
-      for (int cc = 0; cc < HD / 32; ++cc) {
-        mfma(sh, kf[kt][cc], qf[cc].hi);
-        mfma(sl, kf[kt][cc], qf[cc].lo);
+      for (int t = 0; t < 4; ++t) {
+        const int rr = 32 * (t >> 1) + 8 * (ql >> 2) + 4 * (t & 1) + (ql & 3);
+        Frag<bf16_t> kf;
+        kf.v = lk[16 * rr + ((kg + 4 * cc) ^ kswz(rr))];
+        mfma(sh[t], kf, qf[cc].hi);
+        mfma(sl[t], kf, qf[cc].lo);
       }
-      sc[kt] = sh + sl;
-    }
-    const uint32_t vis = low_bits8(lim - key0) & (low_bits8(C - key0) | vis_bits8(vw, key0 - C));
-    float p[8];
-    float mx = -INFINITY;
+    float p[16];  // p[8 h + e]: key kp0 + 32 h + 8 kg + e
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
+    for (int e = 0; e < 16; ++e) p[e] = sh[e >> 2][e & 3] + sl[e >> 2][e & 3];
+    if (kp0 + kPage > min(C, lim)) {  // block-uniform: pages inside the prefix have no mask to apply
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int e = kt * 4 + i;
-        const float v = ((vis >> e) & 1u) ? sc[kt][i] * scale : -INFINITY;
-        p[e] = v;
-        mx = fmaxf(mx, v);
+      for (int h = 0; h < 2; ++h) {
+        const int key0 = kp0 + 32 * h + 8 * kg;
+        const uint32_t vis = low_bits8(lim - key0) & (low_bits8(C - key0) | vis_bits8(vw, key0 - C));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[8 * h + e] = ((vis >> e) & 1u) ? p[8 * h + e] : -INFINITY;
       }
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float m_new = fmaxf(m_run, mx);
+    }
+    float mx = p[0];
+#pragma unroll
+    for (int e = 1; e < 16; ++e) mx = fmaxf(mx, p[e]);
+    const float m_new = fmaxf(m_run, column_max(mx) * scale);
     const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
     float psum = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      p[e] = __builtin_amdgcn_exp2f(p[e] - m_use);
+    for (int e = 0; e < 16; ++e) {
+      p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(p[e], scale, -m_use));
       psum += p[e];
     }
     l_run = l_run * alpha + psum;
+    // the maximum rarely moves after the first pages: alpha is 1 then
+    if (!__all(m_new == m_run)) {
+#pragma unroll
+      for (int dt = 0; dt < HD / 16; ++dt) o[dt] *= alpha;
+    }
     m_run = m_new;
-    const PFrag<bf16_t> pf = pfrag<bf16_t>(p);
 #pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) o[dt] *= alpha;
+    for (int h = 0; h < 2; ++h) {
+      const PFrag<bf16_t> pf = pfrag<bf16_t>(p + 8 * h);
 #pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) mfma(o[dt], vf[dt], pf.hi);
-#pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) mfma(o[dt], vf[dt], pf.lo);
+      for (int dt = 0; dt < HD / 16; ++dt) {
+        const int d = dt * 16 + ql, pc = 4 * h + kg;
+        Frag<bf16_t> vf;
+        vf.v = lv[8 * d + (pc ^ ((d >> 1) & 7))];
+        mfma(o[dt], vf, pf.hi);
+        mfma(o[dt], vf, pf.lo);
+      }
+    }
   };
 
   // pages through a two-deep register ring and two LDS buffers; waves
@@ -560,19 +601,13 @@ __global__ void __launch_bounds__(512, 1) k_attn_lds(AttnArgs a) {
     for (; i + 2 <= npg; i += 2) {
 #pragma unroll
       for (int slot = 0; slot < 2; ++slot) {
-        if (active) {
-          compute(slot, k0 + (i + slot) * kPage, 0);
-          compute(slot, k0 + (i + slot) * kPage, 1);
-        }
+        if (active) compute(slot, k0 + (i + slot) * kPage);
         load_page(ring[slot], i + slot + 2);
         store_page(ring[slot ^ 1], slot ^ 1);
         __syncthreads();
       }
     }
-    if (i < npg && active) {                               // an odd last page, in buffer 0
-      compute(0, k0 + i * kPage, 0);
-      compute(0, k0 + i * kPage, 1);
-    }
+    if (i < npg && active) compute(0, k0 + i * kPage);     // an odd last page, in buffer 0
   }
   if (!active) return;
 
@@ -587,11 +622,11 @@ __global__ void __launch_bounds__(512, 1) k_attn_lds(AttnArgs a) {
   if (S == 1) {
     const float inv = 1.f / lr;
 #pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        act_store<bf16_t>(reinterpret_cast<bf16_t*>(a.out) + act_offset(r, head * HD + dt * 16 + 4 * kg + i, a.H * HD),
-                          a.out_plane, o[dt][i] * inv);
+    for (int dt = 0; dt < HD / 16; ++dt) {
+      const float v[4] = {o[dt][0] * inv, o[dt][1] * inv, o[dt][2] * inv, o[dt][3] * inv};
+      act_store4<bf16_t>(reinterpret_cast<bf16_t*>(a.out) + act_offset(r, head * HD + dt * 16 + 4 * kg, a.H * HD),
+                         a.out_plane, v);
+    }
   } else {
     float* op = a.o_part + ((size_t)split * nrow + qidx) * HD + 4 * kg;
 #pragma unroll
@@ -669,18 +704,18 @@ static hipError_t launch_attn_t(const AttnArgs& a, hipStream_t st) {
   const int nq = (a.H / a.G) * a.R;
   const int ntiles = (nq + 15) / 16;
   // two query tiles per block: bf16 only (measured there; the fp32 kernel
-  // has no registers to spare)
-  bool two = false;
-  if constexpr (sizeof(T) == 2) two = a.qt == 2;
-  if (two) {
-    if constexpr (sizeof(T) == 2)
+  // has no registers to spare), and not at the LDS-shared form's head_dim,
+  // which takes that work itself
+  constexpr bool kTwo = sizeof(T) == 2 && HD != kAttnLdsHD;
+  if (kTwo && a.qt == 2) {
+    if constexpr (kTwo)
       hipLaunchKernelGGL((k_attn<T, HD, 2>), dim3(a.G, (ntiles + 1) / 2, a.splits), dim3(256), 0, st, a);
   } else {
     hipLaunchKernelGGL((k_attn<T, HD, 1>), dim3(a.G, ntiles, a.splits), dim3(256), 0, st, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.splits == 1) return e;
-  const dim3 grid(a.G, ntiles, HD / 32);
+  const dim3 grid(a.G, ntiles, HD / combine_dims(HD));
   if (a.splits <= 4)
     hipLaunchKernelGGL((k_attn_combine<T, HD, 4>), grid, dim3(256), 0, st, a);
   else if (a.splits <= 8)
@@ -737,7 +772,7 @@ static hipError_t launch_attn_lds(const AttnArgs& a, hipStream_t st) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.splits == 1) return e;
   constexpr int HD = kAttnLdsHD;
-  const dim3 grid(a.G, ntiles, HD / 32);
+  const dim3 grid(a.G, ntiles, HD / combine_dims(HD));
   if (a.splits <= 4)
     hipLaunchKernelGGL((k_attn_combine<bf16_t, HD, 4>), grid, dim3(256), 0, st, a);
   else if (a.splits <= 8)
