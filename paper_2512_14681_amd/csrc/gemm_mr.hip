@@ -106,13 +106,16 @@ static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus) {
 // long K, and matrices that give every compute unit 8 column tiles (32
 // rows: gate/up 60.6 -> 47.7, down 36.4 -> 32.9, LM head 218 -> 211, but
 // QKV 16.2 -> 18.1); up to 24 rows only what one round of workgroups holds
-// (24 rows: gate/up 56.0 -> 47.5, LM head 198 -> 210).  Up to 16 rows none
-// (16 rows: gate/up 47.7 -> 47.5, QKV 12.8 -> 18.1).
+// (24 rows: gate/up 56.0 -> 47.5, LM head 198 -> 210).  10 to 16 rows those
+// too (gate/up at 10 / 16 rows 47.5 -> 46.4 / 48.0 -> 46.1; at 8 rows 45.8
+// -> 46.2), fewer rows none.
 static bool mr_takes(int R, int N, int K, int cus) {
   const int T = N / 16;
   const bool long_k = K >= 8192;
-  if (R <= 16) return false;
-  if (R <= 24) return long_k || (T >= 8 * cus && T <= 12 * cus);
+  const bool one_round = T >= 8 * cus && T <= 12 * cus;
+  if (R < 10) return false;
+  if (R <= 16) return one_round;
+  if (R <= 24) return long_k || one_round;
   if (R <= 32) return long_k || T >= 8 * cus;
   if (R <= 64) return (long)N * K >= 16000000;
   return true;

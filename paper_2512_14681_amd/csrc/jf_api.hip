@@ -384,8 +384,8 @@ static int device_cus() {
 }
 
 // One projection Y[R][N] = X[R][K] W^T with epilogue ep: the many-row kernel
-// (gemm_mr.h) for bf16 where its plan takes the shape (from 17, 25, 33 or 65
-// rows, by the matrix), else the weight-streaming kernel.  The many-row
+// (gemm_mr.h) for bf16 where its plan takes the shape (from 10, 17, 25, 33 or
+// 65 rows, by the matrix), else the weight-streaming kernel.  The many-row
 // kernel's loads go straight to LDS, 16 bytes a lane, and need operands
 // aligned to that.  *part_blocks (if not null) gets the number of per-row
 // argmax key slots the launch writes (EPI_ARGMAX).  split_k = false keeps K
