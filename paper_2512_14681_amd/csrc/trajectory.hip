@@ -24,6 +24,7 @@ namespace {
 
 constexpr int kSelWaves = 4;   // waves (blocks of tokens) per workgroup
 constexpr int kSelBatch = 8;   // loads issued back to back per wave
+constexpr int kStreamHint = 2;   // cache policy of a buffer load: nontemporal (each point is read once)
 constexpr int kBufferFlags = 0x00020000;  // buffer descriptor word 3 (gfx9 family): 32-bit raw data
 
 __global__ void __launch_bounds__(256) k_traj_record(const int32_t* prev, const int32_t* __restrict__ g,
@@ -198,6 +199,96 @@ __global__ void __launch_bounds__(256) k_traj_select_multi(const int32_t* __rest
   if (mine) sel[b0 + lane] = res;
 }
 
+// The same choice, without the counts, for n = 16 or 32 (Q = n / 4 lanes a
+// point) and at least two points: a lane loads four tokens at once, so a
+// block of 16 is one 16-byte load for its points before the fixed point and
+// one for the fixed point itself (whose own count is 0), where the kernel
+// above issues six 4-byte loads and a ballot, a compare and a select for
+// each.  The counts are summed over a point's Q lanes and the keys minimised
+// over the wave in DPP steps: about 30 vector instructions a block instead of
+// 70, which bounded it.  The loads carry the streaming hint (each point is
+// read once; 33.6 -> 32.4 us).  2^18 blocks, us, there -> here: n = 16 35.3
+// -> 33.0 (two devices), n = 32 96.5 -> 85.8.  It is not used for n = 8 (16 of 64 lanes
+// would load: 32.8 -> 34.0) and with counts (a store of 16 or 8 lanes per load
+// instead of one per block: n = 16 41.1 -> 42.4, n = 32 111 -> 121).
+// K loads hold max_points - 1 points: 64 K >= (max_points - 1) Q.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_min(int x) {
+  return min(x, __builtin_amdgcn_update_dpp(x, x, CTRL, ROWS, 0xF, false));
+}
+template <int CTRL>
+__device__ __forceinline__ int dpp_add(int x) {
+  return x + __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, false);
+}
+
+template <int B, int K, int Q>
+__global__ void __launch_bounds__(256) k_traj_select_wide(const int32_t* __restrict__ traj,
+                                                          const int32_t* __restrict__ len, int n_blocks,
+                                                          int max_points, int w, const int32_t* __restrict__ t_num,
+                                                          int32_t* __restrict__ sel) {
+  static_assert(Q == 4 || Q == 8, "lanes a point");
+  typedef int v4i __attribute__((ext_vector_type(4)));
+  constexpr int n = 4 * Q, PP = 64 / Q;                 // tokens of a point, points of a load
+  const int lane = threadIdx.x & 63;
+  // wave-uniform: a scalar register, so the buffer descriptors below are too
+  const int b0 = __builtin_amdgcn_readfirstlane((blockIdx.x * kSelWaves + (threadIdx.x >> 6)) * B);
+  if (b0 >= n_blocks) return;
+  const int pos = lane % Q, pt = lane / Q;
+  const bool mine = lane < B && b0 + lane < n_blocks;   // lane i carries block b0 + i's scalars
+  const int Lr = mine ? len[b0 + lane] : 0;
+  const int tr = mine ? (t_num ? min(max(t_num[b0 + lane], 0), w) : (b0 + lane) % w) : 0;
+  // Loads through buffer descriptors whose ranges are the block's points
+  // before the fixed point, and the fixed point: lanes past them read 0 from
+  // the hardware's range check.
+  v4i v[B][K], ys[B];
+#pragma unroll
+  for (int i = 0; i < B; ++i) {
+    const int L = __builtin_amdgcn_readlane(Lr, i);
+    const int before = (L >= 1 && L <= max_points) ? L - 1 : 0;
+    int32_t* base = const_cast<int32_t*>(traj + (size_t)min(b0 + i, n_blocks - 1) * max_points * n);
+    __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base, 0, before * n * 4, kBufferFlags);
+    __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(base + before * n, 0, n * 4, kBufferFlags);
+#pragma unroll
+    for (int q = 0; q < K; ++q)
+      v[i][q] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, (q * 64 + lane) * 16, 0, kStreamHint));
+    ys[i] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(ry, pos * 16, 0, kStreamHint));
+  }
+  int res = 0;
+#pragma unroll
+  for (int i = 0; i < B; ++i) {
+    const int b = b0 + i;
+    if (b >= n_blocks) break;
+    const int L = __builtin_amdgcn_readlane(Lr, i);
+    if (L < 1 || L > max_points) {
+      if (lane == i) res = -1;
+      continue;
+    }
+    const int tn = __builtin_amdgcn_readlane(tr, i) * n;
+    int key = 0x7FFFFFFF;
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      if (q * PP < L - 1) {                             // uniform: loads past the points hold nothing
+        const v4i x = v[i][q], y = ys[i];
+        int u = (int)(x.x != y.x) + (int)(x.y != y.y) + (int)(x.z != y.z) + (int)(x.w != y.w);
+        u = dpp_add<0xB1>(u);                           // quad_perm [1,0,3,2]
+        u = dpp_add<0x4E>(u);                           // quad_perm [2,3,0,1]
+        if constexpr (Q == 8) u = dpp_add<0x141>(u);    // row_half_mirror
+        const int j = q * PP + pt;
+        const int d = abs((int)__umul24(u, w) - tn);    // u <= 32, w < 2^24
+        key = min(key, j < L - 1 ? (d << 6) | j : 0x7FFFFFFF);
+      }
+    }
+    if constexpr (Q == 4) key = dpp_min<0x141, 0xF>(key);
+    key = dpp_min<0x140, 0xF>(key);                     // row_mirror: the row's minimum in each lane
+    key = dpp_min<0x142, 0xA>(key);                     // row_bcast15 into rows 1 and 3
+    key = dpp_min<0x143, 0xC>(key);                     // row_bcast31 into rows 2 and 3
+    // the fixed point: no token differs, d = tn
+    const int best = min(__builtin_amdgcn_readlane(key, 63), (tn << 6) | (L - 1)) & 63;
+    if (lane == i) res = best;
+  }
+  if (mine) sel[b0 + lane] = res;
+}
+
 }  // namespace
 
 hipError_t launch_traj_record(const int32_t* prev, const int32_t* g, int n, int rows, int32_t* out,
@@ -215,11 +306,26 @@ static void launch_multi(const int32_t* traj, const int32_t* len, int n_blocks, 
                      n_blocks, n, max_points, w, t_num, sel, unconv);
 }
 
+template <int B, int K, int Q>
+static void launch_wide(const int32_t* traj, const int32_t* len, int n_blocks, int max_points, int w,
+                        const int32_t* t_num, int32_t* sel, hipStream_t st) {
+  const int blocks = (n_blocks + kSelWaves * B - 1) / (kSelWaves * B);
+  hipLaunchKernelGGL((k_traj_select_wide<B, K, Q>), dim3(blocks), dim3(64 * kSelWaves), 0, st, traj, len, n_blocks,
+                     max_points, w, t_num, sel);
+}
+
 hipError_t launch_traj_select(const int32_t* traj, const int32_t* len, int n_blocks, int n, int max_points,
                               int w, const int32_t* t_num, int32_t* sel, int32_t* unconv, hipStream_t st) {
   const bool fast = n <= 64 && max_points <= 64 && w < (1 << 24) && (long long)n * w < (1 << 25);
   const int loads = fast ? (max_points + 64 / n - 1) / (64 / n) : 0;
-  if (fast && loads <= 5)
+  // four tokens a lane where the points fit its loads (n + 1 of them, the
+  // most a block that converges has, do)
+  const bool wide = fast && max_points >= 2 && !unconv;
+  if (wide && n == 16 && max_points <= 17)
+    launch_wide<8, 1, 4>(traj, len, n_blocks, max_points, w, t_num, sel, st);
+  else if (wide && n == 32 && max_points <= 33)
+    launch_wide<4, 4, 8>(traj, len, n_blocks, max_points, w, t_num, sel, st);
+  else if (fast && loads <= 5)
     launch_multi<8, 5>(traj, len, n_blocks, n, max_points, w, t_num, sel, unconv, st);
   else if (fast && loads <= 8)
     launch_multi<4, 8>(traj, len, n_blocks, n, max_points, w, t_num, sel, unconv, st);

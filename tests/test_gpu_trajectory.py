@@ -122,6 +122,24 @@ def test_select_equals_oracle(torch_jf, n, nb, w, extra):
     assert unc.tolist() == [want_unc[b] for b in range(nb)]
 
 
+@pytest.mark.parametrize("n,P", [(16, 1), (16, 2), (16, 9), (16, 17), (32, 2), (32, 17), (32, 33)])
+@pytest.mark.parametrize("nb", [3, 1037])
+def test_select_without_counts(torch_jf, n, P, nb):
+    """The four-tokens-a-lane launch (n = 16 and 32, no counts) from one to
+    all of its points: two-valued tokens (equal counts and ties everywhere),
+    every length from 0 to P + 1, a ragged last wave; and that launch against
+    the general one."""
+    torch, jf = torch_jf
+    rng = np.random.default_rng(100 * n + P)
+    traj = rng.integers(0, 2, (nb, P, n)).astype(np.int32)
+    lengths = rng.integers(0, P + 2, nb).astype(np.int32)
+    sel, _ = select_on_gpu(torch, jf, traj, lengths, 16, unconv=False)
+    want, _ = oracle_select(traj, lengths, 16)
+    assert sel.tolist() == [want[b] for b in range(nb)]
+    general, _ = select_on_gpu(torch, jf, traj, lengths, 16)
+    assert sel.tolist() == general.tolist()
+
+
 def test_select_with_a_schedule_table(torch_jf):
     """Per-block targets t_num / w (e.g. the reversed schedule), including
     t = 1 and out-of-range numerators."""
