@@ -34,10 +34,6 @@ template <typename T> struct PFrag;
 template <> struct PFrag<bf16_t> { Frag<bf16_t> hi, lo; };
 template <> struct PFrag<float> { Frag<float> v; };
 
-__device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& lo) {
-  hi = pack_bf16x2(a, b);
-  lo = pack_bf16x2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
-}
 template <typename T> __device__ __forceinline__ PFrag<T> pfrag(const float* p);
 template <> __device__ __forceinline__ PFrag<bf16_t> pfrag<bf16_t>(const float* p) {
   PFrag<bf16_t> f;
@@ -100,20 +96,6 @@ __device__ __forceinline__ float column_max(float v) {
   const uint32_t x = __float_as_uint(w);
   const auto b = __builtin_amdgcn_permlane16_swap(x, x, false, false);
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-
-// Four adjacent columns of a row as activation planes (bf16: one 8-byte store
-// a plane; p is a multiple of 4 elements into the layout's 8-column groups).
-template <typename T> __device__ __forceinline__ void act_store4(T* p, size_t plane, const float (&v)[4]);
-template <> __device__ __forceinline__ void act_store4<bf16_t>(bf16_t* p, size_t plane, const float (&v)[4]) {
-  uint32_t h[2], l[2];
-  split2(v[0], v[1], h[0], l[0]);
-  split2(v[2], v[3], h[1], l[1]);
-  *reinterpret_cast<uint2*>(p) = make_uint2(h[0], h[1]);
-  *reinterpret_cast<uint2*>(p + plane) = make_uint2(l[0], l[1]);
-}
-template <> __device__ __forceinline__ void act_store4<float>(float* p, size_t plane, const float (&v)[4]) {
-  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
 // Low n bits set, n clamped to [0, 8].

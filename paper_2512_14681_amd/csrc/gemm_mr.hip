@@ -13,27 +13,51 @@ namespace jf {
 // Split-K reduction: block (x, y) sums the S partials of rows 16 y .. and
 // columns 64 x .. in split order (deterministic), applies the folded RMSNorm
 // and runs the epilogue (its per-block argmax slot is x).  Each thread owns
-// 4 adjacent columns of one row and keeps 8 partial loads in flight.
+// 4 adjacent columns of one row (the 16 lanes of a row are in one wave) and
+// keeps 8 partial loads in flight.  It is little more than its memory round
+// trips, so the residual and QKV epilogues run in registers on operands
+// loaded along with the partials (residual and gain; position, RoPE row and
+// cache page), with row sums and RoPE partners exchanged between lanes: no
+// LDS tile, no second round trip (192 rows: residual 8.1 -> 7.3 us, QKV 8.2
+// -> 5.6 us a launch; the 64-row step 335.9 -> 325.1 us).
 constexpr int kRedRows = 16, kRedCols = 64, kRedThreads = 256;
 
 __global__ void __launch_bounds__(kRedThreads) k_mr_reduce(MrPlan m, Epi ep) {
-  constexpr int tld = kRedCols + 1;
-  __shared__ float tile[kRedRows * tld];
-  __shared__ float s_rs[kRedRows];
+  constexpr int tld = kRedCols + 4;
+  __shared__ __align__(16) float tile[kRedRows * tld];
   const int N = m.T * 16;
   const int c0 = blockIdx.x * kRedCols, r0 = blockIdx.y * kRedRows;
   const int cols = min(kRedCols, N - c0), rows = min(kRedRows, m.R - r0);
   const size_t split = (size_t)m.R * N;
-  if (ep.ss_in && threadIdx.x < rows) {
-    uint64_t w[3];
-    ss_load(ep.ss_in, ep.ss_stride, r0 + threadIdx.x, w);
-    s_rs[threadIdx.x] = ss_rstd(w, ep.norm_inv_d, ep.norm_eps);
-  }
-  __syncthreads();
   const int r = threadIdx.x / (kRedCols / 4), c = 4 * (threadIdx.x % (kRedCols / 4));
+  const bool mine = r < rows && c < cols;                   // cols is a multiple of 16
+  const int row = r0 + min(r, rows - 1), col = c0 + min(c, cols - 4);
+  const bool resid = ep.kind == EPI_RESID && ep.gain_next, qkv = ep.kind == EPI_QKV;
+  // the epilogue's operands, in flight with the partials
+  uint64_t ssw[3] = {0, 0, 0};
+  if (ep.ss_in) ss_load(ep.ss_in, ep.ss_stride, row, ssw);
+  float4 h = {0.f, 0.f, 0.f, 0.f}, gn = h;                  // residual, gain; or cos, sin
+  int page = 0, slot = 0;
+  // QKV: packed rows are q, k and v heads; RoPE pairs 8 columns apart
+  const int half = ep.hd >> 1;
+  const int head = qkv ? col / ep.hd : 0, w = qkv ? col - head * ep.hd : 0;
+  const int cc = w & 15, ri = 8 * (w >> 4) + (cc & 7);
+  const bool rope = qkv && head < ep.H + ep.G;
+  if (resid) {
+    h = *reinterpret_cast<const float4*>(ep.f32 + (size_t)row * ep.ldf + col);
+    gn = *reinterpret_cast<const float4*>(ep.gain_next + col);
+  } else if (qkv) {
+    slot = ep.state[0] + row;
+    if (head >= ep.H && slot < ep.max_ctx) page = ep.page_table[slot / kPage];
+    if (rope) {
+      const size_t o = (size_t)ep.pos[row] * half + ri;
+      h = *reinterpret_cast<const float4*>(ep.rope_cos + o);
+      gn = *reinterpret_cast<const float4*>(ep.rope_sin + o);
+    }
+  }
   float4 v = {0.f, 0.f, 0.f, 0.f};
-  if (r < rows && c < cols) {                               // cols is a multiple of 16
-    const float4* p = reinterpret_cast<const float4*>(ep.kpart + (size_t)(r0 + r) * N + c0 + c);
+  {
+    const float4* p = reinterpret_cast<const float4*>(ep.kpart + (size_t)row * N + col);
     const size_t sp = split / 4;
     int s = 0;
     for (; s + 8 <= m.S; s += 8) {
@@ -50,17 +74,60 @@ __global__ void __launch_bounds__(kRedThreads) k_mr_reduce(MrPlan m, Epi ep) {
 #pragma unroll
     for (int j = 0; j < 8; ++j)
       if (s + j < m.S) { v.x += x[j].x; v.y += x[j].y; v.z += x[j].z; v.w += x[j].w; }
-    if (ep.ss_in) {
-      const float k = s_rs[r];
-      v.x *= k; v.y *= k; v.z *= k; v.w *= k;
-    }
   }
-  tile[r * tld + c + 0] = v.x;
-  tile[r * tld + c + 1] = v.y;
-  tile[r * tld + c + 2] = v.z;
-  tile[r * tld + c + 3] = v.w;
+  if (ep.ss_in) {
+    const float k = ss_rstd(ssw, ep.norm_inv_d, ep.norm_eps);
+    v.x *= k; v.y *= k; v.z *= k; v.w *= k;
+  }
+  if (resid) {
+    h.x += v.x; h.y += v.y; h.z += v.z; h.w += v.w;
+    float sq = mine ? h.x * h.x + h.y * h.y + h.z * h.z + h.w * h.w : 0.f;
+#pragma unroll
+    for (int o = 1; o < kRedCols / 4; o <<= 1) sq += __shfl_xor(sq, o);
+    if (!mine) return;
+    *reinterpret_cast<float4*>(ep.f32 + (size_t)row * ep.ldf + col) = h;
+    const float x[4] = {h.x * gn.x, h.y * gn.y, h.z * gn.z, h.w * gn.w};
+    act_store4<bf16_t>(reinterpret_cast<bf16_t*>(ep.xg) + act_offset(row, col, ep.ldf), ep.xg_plane, x);
+    if (c == 0) ss_add(ep.ss_out, ep.ss_stride, row, sq);
+    return;
+  }
+  if (qkv) {
+    // the partner columns c ^ 8: two lanes away
+    const float4 y = {__shfl_xor(v.x, 2), __shfl_xor(v.y, 2), __shfl_xor(v.z, 2), __shfl_xor(v.w, 2)};
+    if (!mine) return;
+    float o[4] = {v.x, v.y, v.z, v.w};
+    int dim = w;
+    if (rope) {
+      const float sg = cc < 8 ? -1.f : 1.f;
+      o[0] = v.x * h.x + sg * (y.x * gn.x);
+      o[1] = v.y * h.y + sg * (y.y * gn.y);
+      o[2] = v.z * h.z + sg * (y.z * gn.z);
+      o[3] = v.w * h.w + sg * (y.w * gn.w);
+      dim = cc < 8 ? ri : half + ri;
+    }
+    if (head < ep.H) {
+      act_store4<bf16_t>(reinterpret_cast<bf16_t*>(ep.q) + ((size_t)row * ep.H + head) * ep.hd + dim, ep.q_plane, o);
+      return;
+    }
+    if (slot >= ep.max_ctx) {
+      if (ep.flags) atomicOr(ep.flags, 2);
+      return;
+    }
+    bf16_t* pg = reinterpret_cast<bf16_t*>(ep.kv) + (size_t)page * 2 * ep.G * kPage * ep.hd;
+    const int st = slot % kPage;
+    if (head < ep.H + ep.G) {
+      *reinterpret_cast<uint2*>(pg + ((size_t)(head - ep.H) * kPage + st) * ep.hd + dim) =
+          make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
+    } else {
+      bf16_t* pv = pg + (size_t)ep.G * kPage * ep.hd + ((size_t)(head - ep.H - ep.G) * ep.hd + dim) * kPage + st;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) pv[(size_t)k * kPage] = f32_to_bf16(o[k]);
+    }
+    return;
+  }
+  *reinterpret_cast<float4*>(tile + r * tld + c) = mine ? v : float4{0.f, 0.f, 0.f, 0.f};
   __syncthreads();
-  epilogue<bf16_t>(tile, tld, cols, c0, ep, blockIdx.x, threadIdx.x, kRedThreads, r0, rows);
+  epilogue_wide(tile, tld, cols, c0, ep, blockIdx.x, threadIdx.x, kRedThreads, r0, rows);
 }
 
 // ---- plans ------------------------------------------------------------------------

@@ -135,6 +135,25 @@ template <> __device__ __forceinline__ void act_store<bf16_t>(bf16_t* p, size_t 
 }
 template <> __device__ __forceinline__ void act_store<float>(float* p, size_t plane, float v) { p[0] = v; }
 
+// Two values as hi and lo bf16 pairs.
+__device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& lo) {
+  hi = pack_bf16x2(a, b);
+  lo = pack_bf16x2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
+}
+// Four adjacent columns of a row as activation planes (bf16: one 8-byte store
+// a plane; p is a multiple of 4 elements into the layout's 8-column groups).
+template <typename T> __device__ __forceinline__ void act_store4(T* p, size_t plane, const float (&v)[4]);
+template <> __device__ __forceinline__ void act_store4<bf16_t>(bf16_t* p, size_t plane, const float (&v)[4]) {
+  uint32_t h[2], l[2];
+  split2(v[0], v[1], h[0], l[0]);
+  split2(v[2], v[3], h[1], l[1]);
+  *reinterpret_cast<uint2*>(p) = make_uint2(h[0], h[1]);
+  *reinterpret_cast<uint2*>(p + plane) = make_uint2(l[0], l[1]);
+}
+template <> __device__ __forceinline__ void act_store4<float>(float* p, size_t plane, const float (&v)[4]) {
+  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+}
+
 // acc += A * B with an activation operand on either side.
 __device__ __forceinline__ void mfma(f32x4_t& acc, const ActFrag<bf16_t>& a, const Frag<bf16_t>& b) {
   mfma(acc, a.hi, b);
