@@ -336,50 +336,74 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnArgs a) {
   }
 }
 
-// Merges the splits' (max, sum, O) states of 16 query rows x (up to) 64 dims
-// per block in split order, four dims a thread; every load of a thread is
-// issued at once (SMAX >= S splits unrolled, the extra ones re-reading split
-// S - 1 with weight 0).
-constexpr int combine_dims(int HD) { return HD < 64 ? HD : 64; }
+// Merges the splits' (max, sum, O) states of 16 query rows per block in split
+// order, V dims a thread (16 threads a row; 8 at head_dim 32 with V = 4);
+// every load of a thread is issued at once (SMAX >= S splits unrolled, the
+// extra ones re-reading split S - 1 with weight 0).  V = 4 reads 16 bytes a
+// lane and stores 8; with few query tiles V = 1 spreads the same loads over
+// four times the blocks.
+constexpr int combine_threads(int HD, int V) { return HD / V < 16 ? HD / V : 16; }  // threads of a query row
 
-template <typename T, int HD, int SMAX>
+template <typename T, int HD, int SMAX, int V>
 __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
-  constexpr int DB = combine_dims(HD), TQ = DB / 4;  // dims of a block, threads of a query row
+  constexpr int TQ = combine_threads(HD, V), DB = TQ * V;
   if (threadIdx.x >= 16 * TQ) return;
   const int g = blockIdx.x, tile = blockIdx.y;
   const int S = a.splits;
   const int grp = a.H / a.G, R = a.R, nq = grp * R;
   const size_t nrow = (size_t)R * a.H;
-  const int q = threadIdx.x / TQ, dim = blockIdx.z * DB + 4 * (threadIdx.x % TQ);
+  const int q = threadIdx.x / TQ, dim = blockIdx.z * DB + V * (threadIdx.x % TQ);
   const int qq = min(tile * 16 + q, nq - 1);
   const int hq = qq / R, rr = qq - hq * R;
   const size_t qidx = (size_t)rr * a.H + g * grp + hq;
+  typedef float vec __attribute__((ext_vector_type(V)));
   float2 ml[SMAX];
-  float4 ov[SMAX];
+  vec ov[SMAX];
 #pragma unroll
   for (int sp = 0; sp < SMAX; ++sp) {
     const size_t i = (size_t)min(sp, S - 1) * nrow + qidx;
     ml[sp] = *reinterpret_cast<const float2*>(a.ml_part + i * 2);
-    ov[sp] = *reinterpret_cast<const float4*>(a.o_part + i * HD + dim);
+    ov[sp] = *reinterpret_cast<const vec*>(a.o_part + i * HD + dim);
   }
   float M = -INFINITY;
 #pragma unroll
   for (int sp = 0; sp < SMAX; ++sp) M = fmaxf(M, ml[sp].x);
-  float num[4] = {0.f, 0.f, 0.f, 0.f}, den = 0.f;
+  float num[V] = {}, den = 0.f;
 #pragma unroll
   for (int sp = 0; sp < SMAX; ++sp) {
     const float w = (sp >= S || ml[sp].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml[sp].x - M);
-    num[0] += ov[sp].x * w;
-    num[1] += ov[sp].y * w;
-    num[2] += ov[sp].z * w;
-    num[3] += ov[sp].w * w;
+#pragma unroll
+    for (int k = 0; k < V; ++k) num[k] += ov[sp][k] * w;
     den += ml[sp].y * w;
   }
   if (tile * 16 + q < nq) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) num[k] /= den;
-    act_store4<T>(reinterpret_cast<T*>(a.out) + act_offset(rr, (g * grp + hq) * HD + dim, a.H * HD), a.out_plane, num);
+    for (int k = 0; k < V; ++k) num[k] /= den;
+    T* out = reinterpret_cast<T*>(a.out) + act_offset(rr, (g * grp + hq) * HD + dim, a.H * HD);
+    if constexpr (V == 4) act_store4<T>(out, a.out_plane, num);
+    else act_store<T>(out, a.out_plane, num[0]);
   }
+}
+
+template <typename T, int HD, int V> static void launch_combine_v(const AttnArgs& a, int ntiles, hipStream_t st) {
+  const dim3 grid(a.G, ntiles, HD / (combine_threads(HD, V) * V));
+  if (a.splits <= 4)
+    hipLaunchKernelGGL((k_attn_combine<T, HD, 4, V>), grid, dim3(256), 0, st, a);
+  else if (a.splits <= 8)
+    hipLaunchKernelGGL((k_attn_combine<T, HD, 8, V>), grid, dim3(256), 0, st, a);
+  else if (a.splits <= 16)
+    hipLaunchKernelGGL((k_attn_combine<T, HD, 16, V>), grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_attn_combine<T, HD, 32, V>), grid, dim3(256), 0, st, a);
+}
+// Four dims a thread from 64 query tiles (all KV heads) on.  28 / 4 heads of
+// 128, four dims / one: 1 row after 8000 keys (4 tiles) 14.8 / 13.6 us, 8
+// rows (16) 21.4 / 19.5, 32 rows (56) 26.0 / 25.2; at 84 tiles and more four
+// dims took 2 us off the merge (48 rows 30.8 -> 28.8).
+template <typename T, int HD> static hipError_t launch_combine(const AttnArgs& a, int ntiles, hipStream_t st) {
+  if (a.G * ntiles >= 64) launch_combine_v<T, HD, 4>(a, ntiles, st);
+  else launch_combine_v<T, HD, 1>(a, ntiles, st);
+  return hipGetLastError();
 }
 
 // ---- K/V pages shared through LDS (bf16, head_dim 128) ----------------------------
@@ -697,16 +721,7 @@ static hipError_t launch_attn_t(const AttnArgs& a, hipStream_t st) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.splits == 1) return e;
-  const dim3 grid(a.G, ntiles, HD / combine_dims(HD));
-  if (a.splits <= 4)
-    hipLaunchKernelGGL((k_attn_combine<T, HD, 4>), grid, dim3(256), 0, st, a);
-  else if (a.splits <= 8)
-    hipLaunchKernelGGL((k_attn_combine<T, HD, 8>), grid, dim3(256), 0, st, a);
-  else if (a.splits <= 16)
-    hipLaunchKernelGGL((k_attn_combine<T, HD, 16>), grid, dim3(256), 0, st, a);
-  else
-    hipLaunchKernelGGL((k_attn_combine<T, HD, 32>), grid, dim3(256), 0, st, a);
-  return hipGetLastError();
+  return launch_combine<T, HD>(a, ntiles, st);
 }
 
 static hipError_t launch_checked(int dtype, const AttnArgs& a, hipStream_t st) {
@@ -754,16 +769,7 @@ static hipError_t launch_attn_lds(const AttnArgs& a, hipStream_t st) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.splits == 1) return e;
   constexpr int HD = kAttnLdsHD;
-  const dim3 grid(a.G, ntiles, HD / combine_dims(HD));
-  if (a.splits <= 4)
-    hipLaunchKernelGGL((k_attn_combine<bf16_t, HD, 4>), grid, dim3(256), 0, st, a);
-  else if (a.splits <= 8)
-    hipLaunchKernelGGL((k_attn_combine<bf16_t, HD, 8>), grid, dim3(256), 0, st, a);
-  else if (a.splits <= 16)
-    hipLaunchKernelGGL((k_attn_combine<bf16_t, HD, 16>), grid, dim3(256), 0, st, a);
-  else
-    hipLaunchKernelGGL((k_attn_combine<bf16_t, HD, 32>), grid, dim3(256), 0, st, a);
-  return hipGetLastError();
+  return launch_combine<bf16_t, HD>(a, ntiles, st);
 }
 
 hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t st) {
