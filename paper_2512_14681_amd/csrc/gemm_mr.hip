@@ -145,7 +145,9 @@ static const MrShape kMrShapes[] = {{2, 1, 4, 3}, {4, 1, 2, 6}, {6, 3, 4, 3}, {8
 // of the smaller, and no less than 340 clocks of barrier and load latency.
 // The constants are fitted to 3850 launches (the 7B- and mid-shaped
 // projections, 24 to 512 rows, every shape, split and chunk count); the
-// plans it picks are 1.1% slower than the fastest measured on average.
+// plans it picks are 1.3% slower than the fastest measured on average.  Each
+// further row chunk counts 3%: inside a step many chunks cost more than back
+// to back (QKV at 512 rows in 8 chunks 51.6 us alone, 60 in a prompt chunk).
 static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus) {
   // units go round-robin over the XCDs, the row chunks of a unit to one XCD
   const double units = std::ceil((double)m.n_cg * m.S / 8) * 8;
@@ -161,7 +163,7 @@ static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus) {
   double clocks = rounds * (std::ceil(4.0 * m.KC / m.S) * stage + 14500) + 6500;
   // the partials written and read again (5 TB/s), and the reduction's launch
   if (m.S > 1) clocks += 2.0 * m.S * m.R * m.T * 64 / (2170.0 * cus / 256) + 5200;
-  return clocks * (1 + 0.015 * (m.chunks - 1));
+  return clocks * (1 + 0.03 * (m.chunks - 1));
 }
 
 // Which shapes run here rather than on the weight-streaming kernel (us,
