@@ -696,7 +696,7 @@ def main():
     achieved = gu / avg_s / 1e9
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic(),
-                "kernel": "k_gemm gate/up projection + SwiGLU (28 launches per step)",
+                "kernel": "k_gemm_mr gate/up projection + SwiGLU (28 launches per step)",
                 "bytes_per_launch": gu, "avg_us": round(kern["gateup"]["avg_us"], 2)}
     sb = step_bytes(shape, n, C_mid)
     out = {

@@ -366,6 +366,9 @@ static bool plan_residual(GemmShape& s) {
 // more (three or more chunks).  The rule above over-splits the long-K down
 // projection and, once chunked, keeps too many waves per chunk: the C chunk
 // blocks of a unit already multiply the waves in flight by C.
+// Many of these rows run on the many-row kernel now (mr_takes in gemm_mr.hip);
+// what is left here is fp32 models, operands that are not 16-byte aligned, and
+// O and other small matrices up to 64 rows.
 struct MeasuredPlan { int epi, N, K, NT, WK, S, D; };
 static const MeasuredPlan kPlans32[] = {
     {EPI_RESID, 3584, 18944, 4, 4, 4, 0},    // down: -107 us per n = 32 step vs the rule
