@@ -118,10 +118,10 @@ template <int C, int A> __device__ __forceinline__ void wait_stages(int a) {
 template <bool kStream> __device__ __forceinline__ void dma_1k(const char* src, int lane16, uint32_t dst) {
   if constexpr (kStream)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(dst), "v"(lane16), "s"(src)
-                 : "memory");
+                 : "memory", "m0");
   else
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(lane16), "s"(src)
-                 : "memory");
+                 : "memory", "m0");
 }
 
 template <int MT, int NT> struct MrFrags {
