@@ -169,16 +169,16 @@ def algo_bytes_7b(n, ctx):
 
 def _step_phases(rows, layers):
     """Labels the dispatches of the Jacobi steps in rows [(id, name, value)]
-    by phase, from the launch order of one forward: k_tree_embed, then per layer
-    the QKV projection, attention (+ its split merge), the O projection, the
-    gate/up and the down projection, then the LM head and its tail.  A
-    forward is kept when it ends in an acceptance kernel (k_accept_*, or the
-    fused k_argmax_accept_*: a step, not a prefill chunk).  Returns {phase:
-    [values]}."""
+    by phase, from the launch order of one forward: k_tree_embed (a packed
+    forward: k_tree_packed_embed), then per layer the QKV projection,
+    attention (+ its split merge), the O projection, the gate/up and the down
+    projection, then the LM head and its tail.  A forward is kept when it ends
+    in an acceptance kernel (k_accept_*, or the fused k_argmax_accept_*: a
+    step, not a prefill chunk).  Returns {phase: [values]}."""
     forwards, cur = [], None
     for did, name, v in rows:
         n = short_name(name)
-        if n.startswith(("k_embed", "k_tree_embed")):
+        if n.startswith(("k_embed", "k_tree_embed", "k_tree_packed_embed")):
             cur = []
             forwards.append(cur)
         if cur is not None:

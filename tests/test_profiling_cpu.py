@@ -52,6 +52,20 @@ def test_step_mfma_labels_and_fractions(tmp_path):
     assert out.count("| 0.250 |") >= 6
 
 
+def test_step_phases_ends_a_step_at_a_packed_forward():
+    """Neither a packed forward nor a prefill chunk after a step counts as
+    part of it, under the present kernel names."""
+    layer = ["void jf::k_gemm<unsigned short, 1, 4, 2, 1, false>(int)", "jf::k_attn_lds(jf::AttnArgs)"] + \
+        ["void jf::k_gemm_mr<4, 2, 4, 2, 156>(int)"] * 3
+    head = "void jf::k_gemm_mr<4, 2, 4, 2, 156>(int)"
+    step = ["void jf::k_tree_embed<unsigned short>(int)"] + layer + [head, "jf::k_argmax_accept_linear(int)"]
+    packed = ["void jf::k_tree_packed_embed<unsigned short>(int)"] + layer + [head, "jf::k_argmax_reduce(int)"]
+    rows = [(i, n, 1.0) for i, n in enumerate(step + packed + step[:-2])]
+    out = profiling._step_phases(rows, 1)
+    assert {k: len(v) for k, v in out.items()} == {"k_tree_embed": 1, "qkv": 1, "attn": 1, "o": 1, "gateup": 1,
+                                                   "down": 1, "lm_head": 1, "k_argmax_accept_linear": 1}
+
+
 def write_counter(path, counter, named_values):
     os.makedirs(path, exist_ok=True)
     with open(os.path.join(path, "x_counter_collection.csv"), "w", newline="") as f:
