@@ -5,11 +5,13 @@
 // tree for multi-block / recycled candidates, Sec. 3.2 and App. A Alg. 1).
 //
 // Work split: block (kv head g, 16-query tile, key split), or two query
-// tiles per block for bf16 when query tiles x keys is large (each key chunk
-// then serves both tiles).  The query rows of a KV head are its
-// n_heads/n_kv_heads query heads times R rows, 16 per MFMA tile.  The key splits are laid out over the host's upper bound of
-// C + R, so no address waits on the device's committed length (which only
-// masks), and the split's page-table entries are read once into LDS.  The
+// tiles per block for bf16 at head_dim 32 and 64 when query tiles x keys is
+// large (each key chunk then serves both tiles; head_dim 128 has the
+// LDS-shared form below for that).  The query rows of a KV head are its
+// n_heads/n_kv_heads query heads times R rows, 16 per MFMA tile.  The key
+// splits are laid out over the host's upper bound of C + R, so no address
+// waits on the device's committed length (which only masks), and the split's
+// page-table entries are read once into LDS.  The
 // block's 4 waves take interleaved 32-key chunks with the next chunk's K/V
 // loads in flight: S^T = K Q^T (keys x queries), an fp32 online softmax per
 // query column, then O^T += V^T P^T.  The score tiles' rows are the chunk's
@@ -51,6 +53,7 @@ template <> __device__ __forceinline__ PFrag<float> pfrag<float>(const float* p)
 }
 
 constexpr int kAttnMaxPages = 256;  // pages of one key split (LDS page-table copy)
+constexpr int kAttnCus = 256;       // compute units of an MI355X, for the launch shapes
 
 // Bits j0 .. j0 + 7 of a row's in-step visibility mask (kVisWords words;
 // bits outside [0, kMaxRows) read as 0), branch-free.
@@ -87,9 +90,14 @@ __device__ __forceinline__ void vis_words(const uint64_t* vis, int r, uint64_t (
 }
 
 // Maximum over the four lanes that share a query column (l, l ^ 16, l ^ 32,
-// l ^ 48), on the vector unit: an exchange through LDS costs its latency
-// twice in the middle of every chunk's dependency chain.
-__device__ __forceinline__ float column_max(float v) {
+// l ^ 48).  kPermute: on the vector unit instead of through LDS, whose latency
+// sits twice in the middle of every step's dependency chain; but around the
+// permutes the compiler keeps fewer loads in flight (see k_attn).
+template <bool kPermute> __device__ __forceinline__ float column_max(float v) {
+  if constexpr (!kPermute) {
+    v = fmaxf(v, __shfl_xor(v, 16));
+    return fmaxf(v, __shfl_xor(v, 32));
+  }
   const uint32_t u = __float_as_uint(v);
   const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   const float w = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
@@ -109,7 +117,16 @@ __device__ __forceinline__ uint32_t low_bits8(int n) {
 // tiles.  With QT = 2 one chunk is in
 // flight per wave instead of two (the register budget of two blocks per
 // CU), and the waves' states merge tile after tile.
-template <typename T, int HD, int QT>
+// kPermute (column_max): with the permutes the loads of a chunk are held in
+// fewer registers (fp32 at head_dim 128: 126 against 140, where the K and V
+// fragments alone take 128), which waits for memory more often but fits a
+// fourth block on a compute unit.  So the exchange through LDS everywhere
+// (16 heads of 64, 512 rows after 8000 keys, bf16: 92.2 -> 79.3 us with it)
+// except for fp32 at head_dim 128 where the fourth block saves a round of
+// blocks (28 / 4 heads, permutes / exchange: 1 row after 1024 keys 17.8 /
+// 15.4 us, 320 rows alone 48.6 / 42.2; 16 rows after 8000 keys, 896 blocks,
+// 46.1 / 51.5, 192 rows after 500 42.2 / 48.6).
+template <typename T, int HD, int QT, bool kPermute>
 __global__ void __launch_bounds__(256, 2) k_attn(AttnArgs a) {
   constexpr int NW = 4;  // waves per block
   __shared__ float s_m[NW][16], s_l[NW][16];
@@ -223,7 +240,7 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnArgs a) {
       float mx = p[0];
 #pragma unroll
       for (int e = 1; e < 8; ++e) mx = fmaxf(mx, p[e]);
-      const float m_new = fmaxf(m_run[t], column_max(mx) * scale);
+      const float m_new = fmaxf(m_run[t], column_max<kPermute>(mx) * scale);
       // No branch: the MFMAs need every lane.  A query with nothing visible
       // yet keeps p = 0 and m = -inf.
       const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
@@ -561,7 +578,7 @@ __global__ void __launch_bounds__(512, 1) k_attn_lds(AttnArgs a) {
     float mx = p[0];
 #pragma unroll
     for (int e = 1; e < 16; ++e) mx = fmaxf(mx, p[e]);
-    const float m_new = fmaxf(m_run, column_max(mx) * scale);
+    const float m_new = fmaxf(m_run, column_max<true>(mx) * scale);
     const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
     float psum = 0.f;
@@ -656,7 +673,7 @@ __global__ void __launch_bounds__(512, 1) k_attn_lds(AttnArgs a) {
 constexpr long kAttnQt2Work = 50000;
 
 // The LDS-shared form: query groups of up to 8 tiles (balanced), and key
-// splits of at least 3 pages up to 256 blocks in all: one block runs on a
+// splits of at least 3 pages up to one block a unit in all: one block runs on a
 // compute unit at a time, so a few blocks more than that cost a second round
 // (264 -> 252 blocks at P = 8000 / n = 48: 41.9 -> 37.5 us with the merge;
 // 264 -> 220 at P = 2048 / n = 192: 42.0 -> 32.3 us).  Splits of one
@@ -669,7 +686,7 @@ static void attn_lds_plan(AttnArgs& a) {
   const int groups = (ntiles + 7) / 8;
   a.qg = (ntiles + groups - 1) / groups;
   const int pages = (a.keys_ub + kPage - 1) / kPage;
-  int s = std::max(1, 256 / (a.G * groups));
+  int s = std::max(1, kAttnCus / (a.G * groups));
   s = std::min(s, (pages + 2) / 3);
   const int min_s = (pages + kAttnMaxPages - 3) / (kAttnMaxPages - 2);
   a.splits = std::max(1, std::min(kAttnMaxSplits, std::max(s, min_s)));
@@ -713,11 +730,17 @@ static hipError_t launch_attn_t(const AttnArgs& a, hipStream_t st) {
   // has no registers to spare), and not at the LDS-shared form's head_dim,
   // which takes that work itself
   constexpr bool kTwo = sizeof(T) == 2 && HD != kAttnLdsHD;
+  // fp32 at head_dim 128: 3 blocks a compute unit with the exchange, 4 with
+  // the permutes (k_attn)
+  constexpr bool kBoth = sizeof(T) == 4 && HD == 128;
+  const long blocks = (long)a.G * ntiles * a.splits;
   if (kTwo && a.qt == 2) {
     if constexpr (kTwo)
-      hipLaunchKernelGGL((k_attn<T, HD, 2>), dim3(a.G, (ntiles + 1) / 2, a.splits), dim3(256), 0, st, a);
+      hipLaunchKernelGGL((k_attn<T, HD, 2, false>), dim3(a.G, (ntiles + 1) / 2, a.splits), dim3(256), 0, st, a);
+  } else if (kBoth && (blocks + 4 * kAttnCus - 1) / (4 * kAttnCus) < (blocks + 3 * kAttnCus - 1) / (3 * kAttnCus)) {
+    if constexpr (kBoth) hipLaunchKernelGGL((k_attn<T, HD, 1, true>), dim3(a.G, ntiles, a.splits), dim3(256), 0, st, a);
   } else {
-    hipLaunchKernelGGL((k_attn<T, HD, 1>), dim3(a.G, ntiles, a.splits), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_attn<T, HD, 1, false>), dim3(a.G, ntiles, a.splits), dim3(256), 0, st, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.splits == 1) return e;
