@@ -271,6 +271,11 @@ hipError_t launch_copy_int(int32_t* dst, const int32_t* src, hipStream_t stream)
 // trajectory.hip
 hipError_t launch_traj_record(const int32_t* prev, const int32_t* g, int n, int rows, int32_t* out,
                               hipStream_t stream);
+// kernel of a selection: k_traj_select_wide (n = 16; n = 32 with 1, 3 or 4
+// loads), k_traj_select_multi (with 5, 8 or 17 loads), k_traj_select
+enum SelectForm { SEL_GENERAL = 0, SEL_MULTI_5, SEL_MULTI_8, SEL_MULTI_17, SEL_WIDE_16, SEL_WIDE_32_1, SEL_WIDE_32_3,
+                  SEL_WIDE_32_4 };
+int traj_select_form(int n, int max_points, int w, bool counts);
 hipError_t launch_traj_select(const int32_t* traj, const int32_t* len, int n_blocks, int n, int max_points,
                               int w, const int32_t* t_num, int32_t* sel, int32_t* unconv, hipStream_t stream);
 

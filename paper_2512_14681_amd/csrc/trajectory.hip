@@ -207,11 +207,8 @@ __global__ void __launch_bounds__(256) k_traj_select_multi(const int32_t* __rest
 // each.  The counts are summed over a point's Q lanes and the keys minimised
 // over the wave in DPP steps: about 30 vector instructions a block instead of
 // 70, which bounded it.  The loads carry the streaming hint (each point is
-// read once; 33.6 -> 32.4 us).  2^18 blocks, us, there -> here: n = 16 35.3
-// -> 33.0 (two devices), n = 32 96.5 -> 85.8.  It is not used for n = 8 (16 of 64 lanes
-// would load: 32.8 -> 34.0) and with counts (a store of 16 or 8 lanes per load
-// instead of one per block: n = 16 41.1 -> 42.4, n = 32 111 -> 121).
-// K loads hold max_points - 1 points: 64 K >= (max_points - 1) Q.
+// read once; 33.6 -> 32.4 us).  K loads hold max_points - 1 points: 64 K >=
+// (max_points - 1) Q.  Where it is used: traj_select_form.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ int dpp_min(int x) {
   return min(x, __builtin_amdgcn_update_dpp(x, x, CTRL, ROWS, 0xF, false));
@@ -314,26 +311,46 @@ static void launch_wide(const int32_t* traj, const int32_t* len, int n_blocks, i
                      max_points, w, t_num, sel);
 }
 
+// Which kernel a selection runs on.  Four tokens a lane for n = 16 and 32,
+// without counts, as far as its loads hold the points (n + 1 of them, the
+// most a block that converges has, fit), with the fewest loads that do: one
+// issued for points that are not there costs as much as the others (n = 32 of
+// 5 points with four loads: 32.2 -> 59.4 us).  2^18 blocks of random lengths,
+// us, k_traj_select_multi -> here: n = 16 of 2 / 9 / 17 points 30.9 / 31.8 /
+// 34.0 -> 26.8 / 30.2 / 32.6; n = 32 of 2 / 9 points 31.0 / 34.5 -> 27.6 /
+// 33.2, of 18 / 25 / 33 69.1 / 76.4 / 93.7 -> 60.0 / 66.6 / 83.0 (two blocks a
+// wave there: four leave 2^15 blocks short of waves, 11.7 -> 12.8 of 26
+// points).  Not for n = 32 of 10 to 16 points (10: 35.3 -> 44.1, 13: 42.0 ->
+// 46.4), for n = 8 (16 of 64 lanes would load: 32.8 -> 34.0) and with counts (a
+// store of 16 or 8 lanes a load instead of one a block: n = 16 41.1 -> 42.4,
+// n = 32 111 -> 121).
+int traj_select_form(int n, int max_points, int w, bool counts) {
+  const bool fast = n <= 64 && max_points <= 64 && w < (1 << 24) && (long long)n * w < (1 << 25);
+  if (!fast) return SEL_GENERAL;
+  if (!counts && max_points >= 2) {
+    if (n == 16 && max_points <= 17) return SEL_WIDE_16;
+    if (n == 32 && max_points <= 9) return SEL_WIDE_32_1;
+    if (n == 32 && max_points >= 17 && max_points <= 25) return SEL_WIDE_32_3;
+    if (n == 32 && max_points >= 26 && max_points <= 33) return SEL_WIDE_32_4;
+  }
+  const int loads = (max_points + 64 / n - 1) / (64 / n);
+  return loads <= 5 ? SEL_MULTI_5 : (loads <= 8 ? SEL_MULTI_8 : (loads <= 17 ? SEL_MULTI_17 : SEL_GENERAL));
+}
+
 hipError_t launch_traj_select(const int32_t* traj, const int32_t* len, int n_blocks, int n, int max_points,
                               int w, const int32_t* t_num, int32_t* sel, int32_t* unconv, hipStream_t st) {
-  const bool fast = n <= 64 && max_points <= 64 && w < (1 << 24) && (long long)n * w < (1 << 25);
-  const int loads = fast ? (max_points + 64 / n - 1) / (64 / n) : 0;
-  // four tokens a lane where the points fit its loads (n + 1 of them, the
-  // most a block that converges has, do)
-  const bool wide = fast && max_points >= 2 && !unconv;
-  if (wide && n == 16 && max_points <= 17)
-    launch_wide<8, 1, 4>(traj, len, n_blocks, max_points, w, t_num, sel, st);
-  else if (wide && n == 32 && max_points <= 33)
-    launch_wide<4, 4, 8>(traj, len, n_blocks, max_points, w, t_num, sel, st);
-  else if (fast && loads <= 5)
-    launch_multi<8, 5>(traj, len, n_blocks, n, max_points, w, t_num, sel, unconv, st);
-  else if (fast && loads <= 8)
-    launch_multi<4, 8>(traj, len, n_blocks, n, max_points, w, t_num, sel, unconv, st);
-  else if (fast && loads <= 17)
-    launch_multi<2, 17>(traj, len, n_blocks, n, max_points, w, t_num, sel, unconv, st);
-  else
-    hipLaunchKernelGGL(k_traj_select, dim3((n_blocks + kSelWaves - 1) / kSelWaves), dim3(64 * kSelWaves), 0,
-                       st, traj, len, n_blocks, n, max_points, w, t_num, sel, unconv);
+  switch (traj_select_form(n, max_points, w, unconv != nullptr)) {
+    case SEL_WIDE_16: launch_wide<8, 1, 4>(traj, len, n_blocks, max_points, w, t_num, sel, st); break;
+    case SEL_WIDE_32_1: launch_wide<4, 1, 8>(traj, len, n_blocks, max_points, w, t_num, sel, st); break;
+    case SEL_WIDE_32_3: launch_wide<2, 3, 8>(traj, len, n_blocks, max_points, w, t_num, sel, st); break;
+    case SEL_WIDE_32_4: launch_wide<2, 4, 8>(traj, len, n_blocks, max_points, w, t_num, sel, st); break;
+    case SEL_MULTI_5: launch_multi<8, 5>(traj, len, n_blocks, n, max_points, w, t_num, sel, unconv, st); break;
+    case SEL_MULTI_8: launch_multi<4, 8>(traj, len, n_blocks, n, max_points, w, t_num, sel, unconv, st); break;
+    case SEL_MULTI_17: launch_multi<2, 17>(traj, len, n_blocks, n, max_points, w, t_num, sel, unconv, st); break;
+    default:
+      hipLaunchKernelGGL(k_traj_select, dim3((n_blocks + kSelWaves - 1) / kSelWaves), dim3(64 * kSelWaves), 0, st,
+                         traj, len, n_blocks, n, max_points, w, t_num, sel, unconv);
+  }
   return hipGetLastError();
 }
 

@@ -122,7 +122,8 @@ def test_select_equals_oracle(torch_jf, n, nb, w, extra):
     assert unc.tolist() == [want_unc[b] for b in range(nb)]
 
 
-@pytest.mark.parametrize("n,P", [(16, 1), (16, 2), (16, 9), (16, 17), (32, 2), (32, 17), (32, 33)])
+@pytest.mark.parametrize("n,P", [(16, 1), (16, 2), (16, 9), (16, 17), (32, 2), (32, 9), (32, 10),
+                                 (32, 16), (32, 17), (32, 25), (32, 26), (32, 33)])
 @pytest.mark.parametrize("nb", [3, 1037])
 def test_select_without_counts(torch_jf, n, P, nb):
     """The four-tokens-a-lane launch (n = 16 and 32, no counts) from one to

@@ -1,0 +1,55 @@
+"""Which kernel a call runs on and how its launch is cut: the planners are host
+functions of libjf (paper_2512_14681_amd/csrc/jf_internal.h), called here by
+their C++ names, without a GPU."""
+import ctypes
+import os
+
+import pytest
+
+from paper_2512_14681_amd import jf
+
+I = ctypes.c_int
+SEL_GENERAL, SEL_MULTI_5, SEL_MULTI_8, SEL_MULTI_17, SEL_WIDE_16, SEL_WIDE_32_1, SEL_WIDE_32_3, SEL_WIDE_32_4 = range(8)
+
+
+@pytest.fixture(scope="module")
+def L():
+    if not os.path.exists(jf.LIB_PATH):
+        pytest.skip("libjf.so not built (python -m paper_2512_14681_amd.build)")
+    return ctypes.CDLL(jf.LIB_PATH)
+
+
+# ---- trajectory selection ---------------------------------------------------------
+def select_form(L, n, max_points, w=16, counts=False):
+    f = L._ZN2jf16traj_select_formEiiib
+    f.restype, f.argtypes = I, [I, I, I, ctypes.c_bool]
+    return f(n, max_points, w, counts)
+
+
+def test_selection_loads_match_the_points(L):
+    """No more loads than the points need (the kernel runs one for points
+    that are not there as well), and no fewer: 64 lanes load PP = 16 (n = 16)
+    or 8 (n = 32) points before the fixed point each time."""
+    for P in range(2, 70):
+        f16, f32 = select_form(L, 16, P), select_form(L, 32, P)
+        assert (f16 == SEL_WIDE_16) == (P - 1 <= 16)
+        loads = {SEL_WIDE_32_1: 1, SEL_WIDE_32_3: 3, SEL_WIDE_32_4: 4}.get(f32)
+        if loads:
+            need = (P - 1 + 7) // 8
+            assert need <= loads <= need + (P == 17)
+        else:
+            assert 10 <= P <= 16 or P > 33
+    assert select_form(L, 16, 1) == SEL_MULTI_5 and select_form(L, 32, 1) == SEL_MULTI_5
+
+
+@pytest.mark.parametrize("n,P,w,form", [(8, 9, 16, SEL_MULTI_5), (24, 25, 16, SEL_MULTI_17), (32, 13, 16, SEL_MULTI_8),
+                                        (32, 40, 16, SEL_GENERAL), (65, 5, 16, SEL_GENERAL),
+                                        (16, 65, 16, SEL_GENERAL), (16, 9, 1 << 24, SEL_GENERAL),
+                                        (16, 9, 1 << 21, SEL_GENERAL)])
+def test_selection_general_forms(L, n, P, w, form):
+    assert select_form(L, n, P, w) == form
+
+
+def test_selection_with_counts_keeps_one_store_a_block(L):
+    for n, P in ((16, 17), (32, 5), (32, 33)):
+        assert select_form(L, n, P, counts=True) < SEL_WIDE_16
