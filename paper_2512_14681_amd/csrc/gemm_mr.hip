@@ -144,11 +144,19 @@ static const MrShape kMrShapes[] = {{2, 1, 4, 3}, {4, 1, 2, 6}, {6, 3, 4, 3}, {8
 // weights of all but one of a unit's row chunks), which overlap but for 0.37
 // of the smaller, and no less than 340 clocks of barrier and load latency.
 // The constants are fitted to 3850 launches (the 7B- and mid-shaped
-// projections, 24 to 512 rows, every shape, split and chunk count); the
-// plans it picks are 1.3% slower than the fastest measured on average.  Each
-// further row chunk counts 3%: inside a step many chunks cost more than back
-// to back (QKV at 512 rows in 8 chunks 51.6 us alone, 60 in a prompt chunk).
-static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus) {
+// projections, 24 to 512 rows, every shape, split and chunk count).  Without
+// split K the QKV epilogue (2-byte stores behind RoPE and page loads, element
+// by element) costs 1100 clocks for each element a thread owns, which the
+// reduction's QKV epilogue does not (4608 x 2560 at 448 rows: one split 44.9
+// us, two 35.9).  Each further row chunk counts 3%: launched back to back, with
+// the activations still in every L2, more chunks look cheaper than they are
+// inside a step (three layers, without -> with it: d = 3584 at 224 / 288 rows
+// 868 -> 839 / 1103 -> 1070 us, d = 4096 at 448 rows 1392 -> 1346; it costs
+// short launches, d = 256 and a prompt of 1024 tokens 356 -> 368).  Over 41600
+// launches of 46 matrices (256 to 4096 wide decoders, 17 to 512 rows) the picked
+// plans are 2.6% slower than the fastest on average, 1.6% without the chunks'
+// 3%, 3.8% without the QKV term.
+static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus, int epi_kind) {
   // units go round-robin over the XCDs, the row chunks of a unit to one XCD
   const double units = std::ceil((double)m.n_cg * m.S / 8) * 8;
   const double rounds = std::ceil(units * m.chunks / cus);
@@ -161,6 +169,8 @@ static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus) {
                      2.0 * sh.RT * 1024 / 42;
   const double stage = std::max(std::max(mma, mem) + 0.37 * std::min(mma, mem), 340.0);
   double clocks = rounds * (std::ceil(4.0 * m.KC / m.S) * stage + 14500) + 6500;
+  // a thread's 16 x 16 RT x tiles / 512 elements of the QKV epilogue
+  if (m.S == 1 && epi_kind == EPI_QKV) clocks += rounds * 0.5 * sh.RT * tiles * 1100;
   // the partials written and read again (5 TB/s), and the reduction's launch
   if (m.S > 1) clocks += 2.0 * m.S * m.R * m.T * 64 / (2170.0 * cus / 256) + 5200;
   return clocks * (1 + 0.03 * (m.chunks - 1));
@@ -224,7 +234,7 @@ bool gemm_mr_plan(MrPlan& m, int R, int N, int K, int epi_kind, int n_cus, int m
         const int need = (U + per - 1) / per;
         const long round = std::max(1, cus / (S * t.chunks));
         t.n_cg = (int)std::min<long>(U, need <= round ? round : need);
-        const double c = mr_cost(t, sh, NT, cus);
+        const double c = mr_cost(t, sh, NT, cus, epi_kind);
         if (best < 0 || c < best) {
           best = c;
           m = t;

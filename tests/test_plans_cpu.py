@@ -19,6 +19,34 @@ def L():
     return ctypes.CDLL(jf.LIB_PATH)
 
 
+# ---- many-row GEMM ------------------------------------------------------------------
+EPI_STORE, EPI_RESID, EPI_QKV, EPI_SWIGLU, EPI_ARGMAX = range(5)
+CUS = 256
+
+
+class MrPlan(ctypes.Structure):
+    _fields_ = [(k, I) for k in ("R", "RT", "CT", "KC", "P", "T", "gr", "n_cg", "S", "chunks")]
+
+
+def mr_plan(L, R, N, K, epi, splits=64):
+    """The many-row GEMM's plan of [R][K] x [N][K]^T, or None: another kernel runs it."""
+    f = L._ZN2jf12gemm_mr_planERNS_6MrPlanEiiiiii
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.POINTER(MrPlan), I, I, I, I, I, I]
+    m = MrPlan()
+    return m if f(ctypes.byref(m), R, N, K, epi, CUS, splits) else None
+
+
+@pytest.mark.parametrize("R,N,K", [(320, 4608, 2560), (448, 4608, 2560), (160, 6144, 2560), (320, 6144, 2560),
+                                   (320, 3072, 2048), (448, 3072, 2048), (448, 1280, 1024), (512, 4608, 3584),
+                                   (512, 6144, 4096)])
+def test_qkv_splits_k_where_its_epilogue_would_stall(L, R, N, K):
+    """The QKV epilogue of a workgroup without split K takes longer than the
+    split and its reduction (us, one split -> these plans, in this order: 41.6
+    -> 32.0, 44.9 -> 35.9, 31.7 -> 29.2, 43.5 -> 36.1, 27.9 -> 24.7, 31.7 ->
+    25.9, 18.0 -> 15.4, 52.1 -> 45.5, 64.4 -> 55.9)."""
+    assert mr_plan(L, R, N, K, EPI_QKV).S > 1
+
+
 # ---- trajectory selection ---------------------------------------------------------
 def select_form(L, n, max_points, w=16, counts=False):
     f = L._ZN2jf16traj_select_formEiiib
