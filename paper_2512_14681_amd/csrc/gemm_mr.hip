@@ -181,14 +181,15 @@ static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus, int e
 // 32-row chunks stream the weights three times or more (96 rows: QKV 32.8
 // -> 22.2, O 25.4 -> 21.1).  33 to 64 rows (two chunks): matrices of 16M
 // elements or more (64 rows: gate/up 97 -> 52, QKV 23.7 -> 19.8; smaller
-// ones lose: O 16.3 -> 18.2).  17 to 32 rows (its two-row-tile blocks):
-// long K, and matrices that give every compute unit 8 column tiles (32
-// rows: gate/up 60.6 -> 47.7, down 36.4 -> 32.9, LM head 218 -> 211, but
-// QKV 16.2 -> 18.1); up to 24 rows only what one round of workgroups holds
-// (24 rows: gate/up 56.0 -> 47.5, LM head 198 -> 210).  10 to 16 rows those
-// too (gate/up at 10 / 16 rows 47.5 -> 46.4 / 48.0 -> 46.1; at 8 rows 45.8
-// -> 46.2), fewer rows none.
-static bool mr_takes(int R, int N, int K, int cus) {
+// ones lose: O 16.3 -> 18.2) and long K of any size where K may be split (a
+// down projection of 8192 x 512 / 1024 / 1536 at 64 rows 19.0 / 20.6 / 21.6 ->
+// 12.4 / 14.6 / 17.5).  17 to 32 rows (its two-row-tile blocks): long K, and
+// matrices that give every compute unit 8 column tiles (32 rows: gate/up 60.6
+// -> 47.7, down 36.4 -> 32.9, LM head 218 -> 211, but QKV 16.2 -> 18.1); up to
+// 24 rows only what one round of workgroups holds (24 rows: gate/up 56.0 ->
+// 47.5, LM head 198 -> 210).  10 to 16 rows those too (gate/up at 10 / 16 rows
+// 47.5 -> 46.4 / 48.0 -> 46.1; at 8 rows 45.8 -> 46.2), fewer rows none.
+static bool mr_takes(int R, int N, int K, int cus, bool split) {
   const int T = N / 16;
   const bool long_k = K >= 8192;
   const bool one_round = T >= 8 * cus && T <= 12 * cus;
@@ -196,12 +197,12 @@ static bool mr_takes(int R, int N, int K, int cus) {
   if (R <= 16) return one_round;
   if (R <= 24) return long_k || one_round;
   if (R <= 32) return long_k || T >= 8 * cus;
-  if (R <= 64) return (long)N * K >= 16000000;
+  if (R <= 64) return (long_k && split) || (long)N * K >= 16000000;
   return true;
 }
 
 bool gemm_mr_plan(MrPlan& m, int R, int N, int K, int epi_kind, int n_cus, int max_splits) {
-  if (N % 16 || K % 128 || !mr_takes(R, N, K, std::max(1, n_cus))) return false;
+  if (N % 16 || K % 128 || !mr_takes(R, N, K, std::max(1, n_cus), max_splits > 1)) return false;
   const int gr = epi_kind == EPI_SWIGLU ? 2 : 1;
   if ((N / 16) % gr) return false;
   const int cus = std::max(1, n_cus);

@@ -47,6 +47,14 @@ def test_qkv_splits_k_where_its_epilogue_would_stall(L, R, N, K):
     assert mr_plan(L, R, N, K, EPI_QKV).S > 1
 
 
+def test_long_k_stays_on_the_many_row_kernel(L):
+    """A long-K down projection, however narrow, is on the many-row kernel at
+    every row count from 17 on (its bound once left 33 to 64 rows out)."""
+    for N in (512, 1024, 1536, 1920, 2560):
+        for R in range(17, 129):
+            assert mr_plan(L, R, N, 8192, EPI_RESID), (R, N)
+
+
 # ---- trajectory selection ---------------------------------------------------------
 def select_form(L, n, max_points, w=16, counts=False):
     f = L._ZN2jf16traj_select_formEiiib
