@@ -55,6 +55,23 @@ def test_long_k_stays_on_the_many_row_kernel(L):
             assert mr_plan(L, R, N, 8192, EPI_RESID), (R, N)
 
 
+@pytest.mark.parametrize("R,N,K,here", [
+    (17, 1024, 8192, False), (24, 8192, 8192, False), (32, 4096, 8192, False), (17, 16384, 8192, False),
+    (17, 32768, 8192, True), (32, 32768, 8192, True), (33, 8192, 2048, False), (40, 8192, 5120, False),
+    (33, 12288, 3584, True), (64, 16384, 8192, True), (192, 2048, 3584, False), (256, 2048, 3584, True),
+    (320, 1024, 3584, False), (448, 1024, 8192, False), (448, 2048, 8192, False), (65, 4096, 8192, True),
+    (65, 8192, 1024, True)])
+def test_lm_head_without_split_k_scratch(L, R, N, K, here):
+    """The LM-head component has no scratch for split K: narrow heads and long
+    K stay on the weight-streaming kernel, whose waves share K; with the
+    scratch long K is on the many-row kernel."""
+    m = mr_plan(L, R, N, K, EPI_ARGMAX, splits=1)
+    assert (m is not None) == here
+    assert m is None or m.S == 1
+    if K >= 8192:
+        assert mr_plan(L, R, N, K, EPI_ARGMAX) is not None
+
+
 # ---- trajectory selection ---------------------------------------------------------
 def select_form(L, n, max_points, w=16, counts=False):
     f = L._ZN2jf16traj_select_formEiiib
