@@ -181,37 +181,51 @@ static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus, int e
 // 32-row chunks stream the weights three times or more (96 rows: QKV 32.8
 // -> 22.2, O 25.4 -> 21.1).  33 to 64 rows (two chunks): matrices of 16M
 // elements or more (64 rows: gate/up 97 -> 52, QKV 23.7 -> 19.8; smaller
-// ones lose: O 16.3 -> 18.2) and long K of any size (a down projection of
-// 8192 x 512 / 1024 / 1536 at 64 rows 19.0 / 20.6 / 21.6 -> 12.4 / 14.6 /
-// 17.5).  17 to 32 rows (its two-row-tile blocks): long K, and matrices that
-// give every compute unit 8 column tiles (32 rows: gate/up 60.6 -> 47.7, down
-// 36.4 -> 32.9, LM head 218 -> 211, but QKV 16.2 -> 18.1); up to 24 rows only
-// what one round of workgroups holds (24 rows: gate/up 56.0 -> 47.5, LM head
-// 198 -> 210).  10 to 16 rows those too (gate/up at 10 / 16 rows 47.5 -> 46.4 /
+// ones lose: O 16.3 -> 18.2), of 26M where its two chunks make one full round
+// of 7 or 8 waves a unit (at 48 rows: 4096 x 4096 / 5504 / 6912 / 7552 16.4 /
+// 20.0 / 23.3 / 25.4 -> 20.3 / 21.9 / 23.8 / 24.4, while 4352 x 4096, a round and
+// a bit, 28.8 -> 19.5), and long K of any size (a down projection of 8192 x 512 / 1024 /
+// 1536 at 64 rows 19.0 / 20.6 / 21.6 -> 12.4 / 14.6 / 17.5).  17 to 32 rows
+// (its two-row-tile blocks): long K, and matrices that give every compute unit
+// 8 column tiles (32 rows: gate/up 60.6 -> 47.7, down 36.4 -> 32.9, LM head 218
+// -> 211, but QKV 16.2 -> 18.1); up to 24 rows, where its blocks still load
+// each weight once, long K only of matrices that give most units less than a
+// column tile (N x 8192 at 17 rows: 1024 / 2048 / 3072 16.6 / 17.2 / 18.3 ->
+// 12.9 / 15.9 / 18.3, 3840 / 4096 19.7 / 19.7 -> 20.8 / 21.7), and of the others
+// only what one round of workgroups holds (24 rows: gate/up 56.0 -> 47.5, LM
+// head 198 -> 210).  10 to 16 rows those too (gate/up at 10 / 16 rows 47.5 -> 46.4 /
 // 48.0 -> 46.1; at 8 rows 45.8 -> 46.2), fewer rows none.
 // Without scratch for split K (split false: the LM-head component) a workgroup
 // walks all of K here, where there the waves of a block share it, so long K
 // counts for nothing (LM heads of 1024 / 4096 / 16384 x 8192 at 17 rows 34.5 /
-// 36.2 / 46.4 -> 48.6 / 50.8 / 51.1) and a head of fewer than 3 column tiles a
-// unit stays up to 64 rows (8192 x 2048 / 5120 at 33 rows 15.0 / 29.0 -> 16.4 /
-// 31.7; 12288 x 3584 33.3 -> 28.5), of less than one a unit also beyond while
-// the chunks do not fill the chip (2048 x 3584 at 192 / 256 rows 29.1 / 37.5 ->
-// 33.6 / 24.2) or K is long (1024 / 2048 x 8192 at 448 rows 30.0 / 58.5 -> 61.1
-// / 61.8).
-static bool mr_takes(int R, int N, int K, int cus, bool split) {
+// 36.2 / 46.4 -> 48.6 / 50.8 / 51.1); a head of fewer than 3 column tiles a unit
+// stays up to 64 rows where it makes a full round there (8192 x 2048 / 5120 at
+// 33 rows 15.0 / 29.0 -> 16.4 / 31.7; 12288 x 3584 33.3 -> 28.5), and one of
+// less than a tile a unit stays while the chunks do not fill the chip (2048 x
+// 3584 at 192 / 256 rows 29.1 / 37.5 -> 33.6 / 24.2) or K is long (1024 / 2048 x
+// 8192 at 448 rows 30.0 / 58.5 -> 61.1 / 61.8).
+static bool mr_takes(int R, int N, int K, int epi_kind, int cus, bool split) {
   const int T = N / 16;
   const bool long_k = K >= 8192 && split;
   const bool one_round = T >= 8 * cus && T <= 12 * cus;
   if (R < 10) return false;
   if (R <= 16) return one_round;
-  if (R <= 24) return long_k || one_round;
+  if (R <= 24) return one_round || (long_k && 4 * T <= 3 * cus);
   if (R <= 32) return long_k || T >= 8 * cus;
-  if (R <= 64) return long_k || ((long)N * K >= 16000000 && (split || T >= 3 * cus));
+  if (R <= 64) {
+    if (long_k) return true;
+    GemmShape g{R, N, K, 1, 1, 1};
+    gemm_plan(g, epi_kind);
+    const long waves = (long)gemm_blocks(g) * g.S * g.C * g.WK;
+    const bool full = waves >= 7 * cus && waves <= 8 * cus;
+    if (full && !split && T < 3 * cus) return false;
+    return (long)N * K >= (full ? 26000000 : 16000000);
+  }
   return split || T >= cus || (K < 8192 && (long)R * T > 96 * cus);
 }
 
 bool gemm_mr_plan(MrPlan& m, int R, int N, int K, int epi_kind, int n_cus, int max_splits) {
-  if (N % 16 || K % 128 || !mr_takes(R, N, K, std::max(1, n_cus), max_splits > 1)) return false;
+  if (N % 16 || K % 128 || !mr_takes(R, N, K, epi_kind, std::max(1, n_cus), max_splits > 1)) return false;
   const int gr = epi_kind == EPI_SWIGLU ? 2 : 1;
   if ((N / 16) % gr) return false;
   const int cus = std::max(1, n_cus);

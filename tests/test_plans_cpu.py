@@ -9,7 +9,8 @@ import pytest
 from paper_2512_14681_amd import jf
 
 I = ctypes.c_int
-SEL_GENERAL, SEL_MULTI_5, SEL_MULTI_8, SEL_MULTI_17, SEL_WIDE_16, SEL_WIDE_32_1, SEL_WIDE_32_3, SEL_WIDE_32_4 = range(8)
+(SEL_GENERAL, SEL_MULTI_5, SEL_MULTI_8, SEL_MULTI_17, SEL_WIDE_16, SEL_WIDE_32_1, SEL_WIDE_32_3,
+ SEL_WIDE_32_4) = range(8)
 
 
 @pytest.fixture(scope="module")
@@ -49,10 +50,28 @@ def test_qkv_splits_k_where_its_epilogue_would_stall(L, R, N, K):
 
 def test_long_k_stays_on_the_many_row_kernel(L):
     """A long-K down projection, however narrow, is on the many-row kernel at
-    every row count from 17 on (its bound once left 33 to 64 rows out)."""
-    for N in (512, 1024, 1536, 1920, 2560):
+    every row count from 17 on (its bound once left 33 to 64 rows out), one of
+    nearly a column tile a unit or more from 25."""
+    for N in (512, 1024, 1536, 1920, 2560, 3072):
         for R in range(17, 129):
             assert mr_plan(L, R, N, 8192, EPI_RESID), (R, N)
+    for N in (3840, 4096):
+        for R in range(17, 129):
+            assert (mr_plan(L, R, N, 8192, EPI_RESID) is not None) == (R >= 25), (R, N)
+
+
+@pytest.mark.parametrize("N,K,epi,here", [
+    (4096, 4096, EPI_RESID, False), (4096, 6144, EPI_RESID, False), (3712, 5120, EPI_RESID, False),
+    (4096, 7552, EPI_RESID, True), (2560, 6912, EPI_RESID, True), (3072, 5504, EPI_RESID, True),
+    (3584, 3584, EPI_RESID, False), (8192, 2048, EPI_ARGMAX, False), (8192, 3584, EPI_ARGMAX, True),
+    (8208, 2048, EPI_ARGMAX, True), (4608, 3584, EPI_QKV, True), (4352, 4096, EPI_QKV, True),
+    (6144, 4096, EPI_QKV, True),
+    (16384, 2048, EPI_SWIGLU, True), (37888, 3584, EPI_SWIGLU, True)])
+def test_33_to_64_rows_by_what_the_streaming_kernel_fills(L, N, K, epi, here):
+    """Matrices whose two row chunks make one full round of the
+    weight-streaming kernel's workgroups stay on it up to 26M elements."""
+    for R in (33, 48, 64):
+        assert (mr_plan(L, R, N, K, epi) is not None) == here
 
 
 @pytest.mark.parametrize("R,N,K,here", [
@@ -68,7 +87,7 @@ def test_lm_head_without_split_k_scratch(L, R, N, K, here):
     m = mr_plan(L, R, N, K, EPI_ARGMAX, splits=1)
     assert (m is not None) == here
     assert m is None or m.S == 1
-    if K >= 8192:
+    if K >= 8192 and R >= 25:
         assert mr_plan(L, R, N, K, EPI_ARGMAX) is not None
 
 
