@@ -193,8 +193,12 @@ static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus, int e
 // column tile (N x 8192 at 17 rows: 1024 / 2048 / 3072 16.6 / 17.2 / 18.3 ->
 // 12.9 / 15.9 / 18.3, 3840 / 4096 19.7 / 19.7 -> 20.8 / 21.7), and of the others
 // only what one round of workgroups holds (24 rows: gate/up 56.0 -> 47.5, LM
-// head 198 -> 210).  10 to 16 rows those too (gate/up at 10 / 16 rows 47.5 -> 46.4 /
-// 48.0 -> 46.1; at 8 rows 45.8 -> 46.2), fewer rows none.
+// head 198 -> 210).  10 to 16 rows: of those, the ones whose 64-column groups do
+// not make full rounds there (gate/up at 10 / 16 rows in a step 47.5 -> 46.4 /
+// 48.0 -> 46.1, at 8 rows 45.8 -> 46.2; 40960 x 512 / 2048, two and a half rounds,
+// at 10 rows 14.0 / 31.9 -> 12.4 / 30.4, but 49152 x 1024 and 32768 x 3072, three
+// and two, 19.7 / 34.9 -> 20.9 / 36.4), and a step's LM head (49152 x 256 / 32768
+// x 3584 10.8 / 41.8 -> 10.1 / 40.4).  Fewer rows: none.
 // Without scratch for split K (split false: the LM-head component) a workgroup
 // walks all of K here, where there the waves of a block share it, so long K
 // counts for nothing (LM heads of 1024 / 4096 / 16384 x 8192 at 17 rows 34.5 /
@@ -209,7 +213,7 @@ static bool mr_takes(int R, int N, int K, int epi_kind, int cus, bool split) {
   const bool long_k = K >= 8192 && split;
   const bool one_round = T >= 8 * cus && T <= 12 * cus;
   if (R < 10) return false;
-  if (R <= 16) return one_round;
+  if (R <= 16) return one_round && (T % (4 * cus) != 0 || (split && epi_kind == EPI_ARGMAX));
   if (R <= 24) return one_round || (long_k && 4 * T <= 3 * cus);
   if (R <= 32) return long_k || T >= 8 * cus;
   if (R <= 64) {

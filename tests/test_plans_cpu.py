@@ -74,6 +74,20 @@ def test_33_to_64_rows_by_what_the_streaming_kernel_fills(L, N, K, epi, here):
         assert (mr_plan(L, R, N, K, epi) is not None) == here
 
 
+@pytest.mark.parametrize("N,K,epi,splits,here", [
+    (37888, 3584, EPI_SWIGLU, 64, True), (40960, 512, EPI_SWIGLU, 64, True), (49152, 1024, EPI_SWIGLU, 64, False),
+    (32768, 3072, EPI_SWIGLU, 64, False), (28672, 4096, EPI_SWIGLU, 64, False), (49152, 256, EPI_ARGMAX, 64, True),
+    (49152, 256, EPI_ARGMAX, 1, False), (40960, 2048, EPI_ARGMAX, 1, True), (152064, 3584, EPI_ARGMAX, 64, False)])
+def test_10_to_16_rows_where_the_streaming_rounds_are_uneven(L, N, K, epi, splits, here):
+    """Few rows go to the many-row kernel where one round of its workgroups
+    holds the matrix and the weight-streaming kernel's last round is partly
+    empty, and for a step's LM head of that width."""
+    for R in (1, 8, 9):
+        assert mr_plan(L, R, N, K, epi, splits) is None
+    for R in (10, 13, 16):
+        assert (mr_plan(L, R, N, K, epi, splits) is not None) == here
+
+
 @pytest.mark.parametrize("R,N,K,here", [
     (17, 1024, 8192, False), (24, 8192, 8192, False), (32, 4096, 8192, False), (17, 16384, 8192, False),
     (17, 32768, 8192, True), (32, 32768, 8192, True), (33, 8192, 2048, False), (40, 8192, 5120, False),
@@ -114,10 +128,9 @@ def test_selection_loads_match_the_points(L):
     assert select_form(L, 16, 1) == SEL_MULTI_5 and select_form(L, 32, 1) == SEL_MULTI_5
 
 
-@pytest.mark.parametrize("n,P,w,form", [(8, 9, 16, SEL_MULTI_5), (24, 25, 16, SEL_MULTI_17), (32, 13, 16, SEL_MULTI_8),
-                                        (32, 40, 16, SEL_GENERAL), (65, 5, 16, SEL_GENERAL),
-                                        (16, 65, 16, SEL_GENERAL), (16, 9, 1 << 24, SEL_GENERAL),
-                                        (16, 9, 1 << 21, SEL_GENERAL)])
+@pytest.mark.parametrize("n,P,w,form", [
+    (8, 9, 16, SEL_MULTI_5), (24, 25, 16, SEL_MULTI_17), (32, 13, 16, SEL_MULTI_8), (32, 40, 16, SEL_GENERAL),
+    (65, 5, 16, SEL_GENERAL), (16, 65, 16, SEL_GENERAL), (16, 9, 1 << 24, SEL_GENERAL), (16, 9, 1 << 21, SEL_GENERAL)])
 def test_selection_general_forms(L, n, P, w, form):
     assert select_form(L, n, P, w) == form
 
