@@ -198,7 +198,8 @@ static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus, int e
 // 48.0 -> 46.1, at 8 rows 45.8 -> 46.2; 40960 x 512 / 2048, two and a half rounds,
 // at 10 rows 14.0 / 31.9 -> 12.4 / 30.4, but 49152 x 1024 and 32768 x 3072, three
 // and two, 19.7 / 34.9 -> 20.9 / 36.4), and a step's LM head (49152 x 256 / 32768
-// x 3584 10.8 / 41.8 -> 10.1 / 40.4).  Fewer rows: none.
+// x 3584 10.8 / 41.8 -> 10.1 / 40.4) and matrices of 200M elements (32768 x 8192
+// without the scratch 87.7 -> 80.7).  Fewer rows: none.
 // Without scratch for split K (split false: the LM-head component) a workgroup
 // walks all of K here, where there the waves of a block share it, so long K
 // counts for nothing (LM heads of 1024 / 4096 / 16384 x 8192 at 17 rows 34.5 /
@@ -213,7 +214,9 @@ static bool mr_takes(int R, int N, int K, int epi_kind, int cus, bool split) {
   const bool long_k = K >= 8192 && split;
   const bool one_round = T >= 8 * cus && T <= 12 * cus;
   if (R < 10) return false;
-  if (R <= 16) return one_round && (T % (4 * cus) != 0 || (split && epi_kind == EPI_ARGMAX));
+  if (R <= 16)
+    return one_round &&
+           (T % (4 * cus) != 0 || (split && epi_kind == EPI_ARGMAX) || (long)N * K >= 200000000);
   if (R <= 24) return one_round || (long_k && 4 * T <= 3 * cus);
   if (R <= 32) return long_k || T >= 8 * cus;
   if (R <= 64) {

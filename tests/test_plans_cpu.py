@@ -77,11 +77,12 @@ def test_33_to_64_rows_by_what_the_streaming_kernel_fills(L, N, K, epi, here):
 @pytest.mark.parametrize("N,K,epi,splits,here", [
     (37888, 3584, EPI_SWIGLU, 64, True), (40960, 512, EPI_SWIGLU, 64, True), (49152, 1024, EPI_SWIGLU, 64, False),
     (32768, 3072, EPI_SWIGLU, 64, False), (28672, 4096, EPI_SWIGLU, 64, False), (49152, 256, EPI_ARGMAX, 64, True),
-    (49152, 256, EPI_ARGMAX, 1, False), (40960, 2048, EPI_ARGMAX, 1, True), (152064, 3584, EPI_ARGMAX, 64, False)])
+    (49152, 256, EPI_ARGMAX, 1, False), (40960, 2048, EPI_ARGMAX, 1, True), (152064, 3584, EPI_ARGMAX, 64, False),
+    (32768, 8192, EPI_ARGMAX, 1, True)])
 def test_10_to_16_rows_where_the_streaming_rounds_are_uneven(L, N, K, epi, splits, here):
     """Few rows go to the many-row kernel where one round of its workgroups
     holds the matrix and the weight-streaming kernel's last round is partly
-    empty, and for a step's LM head of that width."""
+    empty, for a step's LM head of that width, and for very large ones."""
     for R in (1, 8, 9):
         assert mr_plan(L, R, N, K, epi, splits) is None
     for R in (10, 13, 16):
