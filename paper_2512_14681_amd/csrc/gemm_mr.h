@@ -262,8 +262,98 @@ __device__ __forceinline__ void mr_kloop(f32x4_t (&acc)[Cfg::ACC][MT][NT], const
   }
 }
 
-template <int MT, int NT, int WM, int WN, int KB>
-__global__ void __launch_bounds__(kMrThreads, KB <= 80 ? 4 : 2)
+// The K loop for operands off a 16-byte boundary, which the loads above do not
+// take: every wave brings C pieces a fragment step through registers, two
+// stages of two steps ahead, into two LDS slots (stage s + 1 is written while
+// stage s is read; the barrier between them waits for LDS only, so the loads
+// stay in flight).  Piece i of a wave comes from src[i] and goes to dst[i] of
+// slot 0; the weight pieces (isw[i]) advance by K-blocks of kstride bytes, the
+// others are contiguous, and a step's pieces of the two kinds are WP and XP apart
+// in a slot.  A piece with on[i] false (a wave's last) re-reads another and is
+// not written.
+template <int C> struct MrAnyPieces {
+  const char* src[C];
+  char* dst[C];
+  bool isw[C], on[C];
+};
+template <typename Cfg, int MT, int NT, int C>
+__device__ __forceinline__ void mr_kloop_any(f32x4_t (&acc)[Cfg::ACC][MT][NT], const MrAnyPieces<C>& pc, int s0, int nst,
+                                             size_t kstride, const char* rx, const char* rw, int lane16) {
+  static_assert(Cfg::DX >= 4 && Cfg::DW >= 4, "two slots of two steps");
+  u32x4_t stg[2][2][C];
+  auto load = [&](u32x4_t (&r)[2][C], int s) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int f = s0 + 2 * s + j;
+      const size_t wo = (size_t)(f >> 2) * kstride + (size_t)(f & 3) * 1024, xo = (size_t)f * 1024;
+#pragma unroll
+      for (int i = 0; i < C; ++i)
+        r[j][i] = *reinterpret_cast<const u32x4_t*>(pc.src[i] + (pc.isw[i] ? wo : xo) + lane16);
+    }
+  };
+  auto store = [&](const u32x4_t (&r)[2][C], int slot) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int i = 0; i < C; ++i)
+        if (pc.on[i])
+          *reinterpret_cast<u32x4_t*>(pc.dst[i] + (2 * slot + j) * (pc.isw[i] ? Cfg::WP : Cfg::XP) * 1024 + lane16) =
+              r[j][i];
+  };
+  auto barrier = [] {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  auto compute = [&](int slot) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const char *px = rx + (2 * slot + j) * (Cfg::XP * 1024), *pw = rw + (2 * slot + j) * (Cfg::WP * 1024);
+      uint4 w[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) w[t] = *reinterpret_cast<const uint4*>(pw + t * 1024);
+#pragma unroll
+      for (int k = 0; k < 2 * MT; ++k) {
+        const uint4 x = *reinterpret_cast<const uint4*>(px + k * 1024);
+        const int a = Cfg::ACC == 4 ? 2 * j + (k & 1) : (Cfg::ACC == 2 ? k & 1 : 0);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          acc[a][k >> 1][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(bf16x8_t, x), __builtin_bit_cast(bf16x8_t, w[t]), acc[a][k >> 1][t], 0, 0, 0);
+      }
+    }
+  };
+  const int ns = nst / 2;                     // stages (nst is even)
+  load(stg[0], 0);
+  if (ns > 1) load(stg[1], 1);
+  store(stg[0], 0);
+  barrier();
+  int s = 0;
+#pragma unroll 1
+  for (; s + 4 <= ns; s += 2) {
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      compute(d);
+      load(stg[d], s + d + 2);
+      store(stg[d ^ 1], d ^ 1);
+      barrier();
+    }
+  }
+  // fewer than 4 stages left
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    if (s + d < ns) {
+      compute(d & 1);
+      if (s + d + 2 < ns) load(stg[d & 1], s + d + 2);
+      if (s + d + 1 < ns) store(stg[(d & 1) ^ 1], (d & 1) ^ 1);
+      barrier();
+    }
+  }
+}
+
+// kAny: operands of any alignment (mr_kloop_any).
+template <int MT, int NT, int WM, int WN, int KB, bool kAny>
+__global__ void __launch_bounds__(kMrThreads, 2)
 k_gemm_mr(const bf16_t* __restrict__ X, size_t xplane, const bf16_t* __restrict__ Wp, MrPlan m, Epi ep) {
   using Cfg = MrCfg<MT, NT, WM, WN, KB>;
   constexpr int XP = Cfg::XP, WP = Cfg::WP, LW = Cfg::LW, CX = Cfg::CX, CW = Cfg::CW;
@@ -287,7 +377,9 @@ k_gemm_mr(const bf16_t* __restrict__ X, size_t xplane, const bf16_t* __restrict_
   const int U = m.T / m.gr;                   // column units
   const int t0 = (int)(((long)U * g) / m.n_cg) * m.gr, t1 = (int)(((long)U * (g + 1)) / m.n_cg) * m.gr;
   const int nt = t1 - t0;                     // column tiles of the group (<= CT)
-  const int s0 = (4 * KC * sk) / m.S, s1 = (4 * KC * (sk + 1)) / m.S;  // fragment steps
+  // fragment steps (kAny: a whole number of its two-step stages)
+  const int s0 = kAny ? (2 * KC * sk) / m.S * 2 : (4 * KC * sk) / m.S;
+  const int s1 = kAny ? (2 * KC * (sk + 1)) / m.S * 2 : (4 * KC * (sk + 1)) / m.S;
   const int nst = s1 - s0;
 
   // Folded RMSNorm: the row sums of squares (a row per thread) are loaded
@@ -310,26 +402,39 @@ k_gemm_mr(const bf16_t* __restrict__ X, size_t xplane, const bf16_t* __restrict_
   auto lds_addr = [](char* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)p; };
   // This wave's pieces (absent row and column tiles re-read the last one, an
   // L2 hit whose products are not stored): bases at fragment step 0.
-  if (wave < LW) {
+  auto w_base = [&](int e) {                  // weight piece e: column tile e of the group
+    const int t = t0 + min(e, nt - 1);
+    return reinterpret_cast<const char*>(Wp + ((size_t)(t / P) * KC * P + t % P) * kBlockElems);
+  };
+  auto x_base = [&](int e) {                  // activation piece e: plane e % 2 of row tile e / 2
+    const int rt = min(e >> 1, rtiles - 1);
+    return reinterpret_cast<const char*>(X + (size_t)(e & 1) * xplane + (((size_t)(r0 / 16 + rt) * KC) << 11));
+  };
+  const size_t ks = (size_t)P * kBlockElems * sizeof(bf16_t);
+  if constexpr (kAny) {
+    constexpr int C = (XP + WP + kMrWaves - 1) / kMrWaves;
+    MrAnyPieces<C> pc;
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+      const int e = wave + kMrWaves * i, ex = min(max(e - WP, 0), XP - 1);
+      pc.isw[i] = e < WP;
+      pc.on[i] = e < WP + XP;
+      pc.src[i] = pc.isw[i] ? w_base(e) : x_base(ex);
+      pc.dst[i] = pc.isw[i] ? lw + e * 1024 : lx + ex * 1024;
+    }
+    mr_kloop_any<Cfg, MT, NT, C>(acc, pc, s0, nst, ks, rx, rw, lane16);
+  } else if (wave < LW) {
     MrLoader<CW> ld;
 #pragma unroll
-    for (int i = 0; i < CW; ++i) {
-      const int t = t0 + min(min(wave + LW * i, WP - 1), nt - 1);
-      ld.src[i] = reinterpret_cast<const char*>(Wp + ((size_t)(t / P) * KC * P + t % P) * kBlockElems);
-    }
+    for (int i = 0; i < CW; ++i) ld.src[i] = w_base(min(wave + LW * i, WP - 1));
     ld.ring = lds_addr(lw + wave * 1024);
     ld.full = wave + LW * (CW - 1) < WP;
-    const size_t ks = (size_t)P * kBlockElems * sizeof(bf16_t);
     if (m.chunks == 1) mr_kloop<Cfg, MT, NT, true, true>(acc, ld, s0, nst, ks, rx, rw, lane16);
     else mr_kloop<Cfg, MT, NT, true, false>(acc, ld, s0, nst, ks, rx, rw, lane16);
   } else {
     MrLoader<CX> ld;
 #pragma unroll
-    for (int i = 0; i < CX; ++i) {
-      const int e = min(wave - LW + (kMrWaves - LW) * i, XP - 1);
-      const int rt = min(e >> 1, rtiles - 1);
-      ld.src[i] = reinterpret_cast<const char*>(X + (size_t)(e & 1) * xplane + (((size_t)(r0 / 16 + rt) * KC) << 11));
-    }
+    for (int i = 0; i < CX; ++i) ld.src[i] = x_base(min(wave - LW + (kMrWaves - LW) * i, XP - 1));
     ld.ring = lds_addr(lx + (wave - LW) * 1024);
     ld.full = wave - LW + (kMrWaves - LW) * (CX - 1) < XP;
     mr_kloop<Cfg, MT, NT, false, false>(acc, ld, s0, nst, 0, rx, rw, lane16);
@@ -395,13 +500,13 @@ k_gemm_mr(const bf16_t* __restrict__ X, size_t xplane, const bf16_t* __restrict_
   }
 }
 
-template <int MT, int NT, int WM, int WN, int KB>
+template <int MT, int NT, int WM, int WN, int KB, bool kAny = false>
 static hipError_t launch_mr_cfg(const void* X, size_t xplane, const void* Wp, const MrPlan& m, const Epi& ep,
                                 hipStream_t st) {
   using Cfg = MrCfg<MT, NT, WM, WN, KB>;
-  if (m.RT != Cfg::RT || m.CT != Cfg::CT) return hipErrorInvalidValue;
+  if (m.RT != Cfg::RT || m.CT != Cfg::CT || m.any != (int)kAny) return hipErrorInvalidValue;
   const unsigned units = (unsigned)m.n_cg * m.S;
-  hipLaunchKernelGGL((k_gemm_mr<MT, NT, WM, WN, KB>), dim3((units + 7) / 8 * 8 * m.chunks), dim3(kMrThreads),
+  hipLaunchKernelGGL((k_gemm_mr<MT, NT, WM, WN, KB, kAny>), dim3((units + 7) / 8 * 8 * m.chunks), dim3(kMrThreads),
                      Cfg::kLds, st, reinterpret_cast<const bf16_t*>(X), xplane, reinterpret_cast<const bf16_t*>(Wp), m,
                      ep);
   return hipGetLastError();

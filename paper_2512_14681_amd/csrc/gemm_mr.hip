@@ -167,7 +167,9 @@ static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus, int e
   const double mma = 64.0 * sh.MT * NT / 0.8;
   const double mem = tiles * 1024 / w_rate / m.chunks + tiles * 1024 / 42 * (m.chunks - 1) / m.chunks +
                      2.0 * sh.RT * 1024 / 42;
-  const double stage = std::max(std::max(mma, mem) + 0.37 * std::min(mma, mem), 340.0);
+  double stage = std::max(std::max(mma, mem) + 0.37 * std::min(mma, mem), 340.0);
+  // operands through registers: matrix work, LDS traffic and the hand-over in turn
+  if (m.any) stage = std::max(stage, mma + (64.0 * (2 * sh.MT + NT) + 8.0 * (2 * sh.RT + m.CT)) / 2 + 280);
   double clocks = rounds * (std::ceil(4.0 * m.KC / m.S) * stage + 14500) + 6500;
   // a thread's 16 x 16 RT x tiles / 512 elements of the QKV epilogue
   if (m.S == 1 && epi_kind == EPI_QKV) clocks += rounds * 0.5 * sh.RT * tiles * 1100;
@@ -231,7 +233,15 @@ static bool mr_takes(int R, int N, int K, int epi_kind, int cus, bool split) {
   return split || T >= cus || (K < 8192 && (long)R * T > 96 * cus);
 }
 
-bool gemm_mr_plan(MrPlan& m, int R, int N, int K, int epi_kind, int n_cus, int max_splits) {
+// Operands off a 16-byte boundary go through registers on their way to LDS
+// (mr_kloop_any), in 64-, 96- and 128-row chunks, from 33 rows on: up to 32 the
+// weight-streaming kernel's blocks load each weight once (the 7B LM head at 32
+// rows 201 us there, 239 here).  Three 7B layers at 48 / 96 / 192 / 320 / 512
+// rows with the weights and the workspace 8 bytes off: 543 / 656 / 993 / 1512 /
+// 1976 us, on the weight-streaming kernel 645 / 888 / 1265 / 1925 / 2958, aligned
+// 443 / 576 / 729 / 1128 / 1528.
+bool gemm_mr_plan(MrPlan& m, int R, int N, int K, int epi_kind, int n_cus, int max_splits, bool aligned) {
+  if (!aligned && R < 33) return false;
   if (N % 16 || K % 128 || !mr_takes(R, N, K, epi_kind, std::max(1, n_cus), max_splits > 1)) return false;
   const int gr = epi_kind == EPI_SWIGLU ? 2 : 1;
   if ((N / 16) % gr) return false;
@@ -239,7 +249,9 @@ bool gemm_mr_plan(MrPlan& m, int R, int N, int K, int epi_kind, int n_cus, int m
   const bool narrow = max_splits > 1 && N / 16 < 8 * std::max(1, cus / ((R + 127) / 128));
   double best = -1;
   for (const MrShape& sh : kMrShapes) {
+    if (!aligned && sh.RT != 4 && sh.RT != 6 && sh.RT != 8) continue;
     MrPlan t{};
+    t.any = !aligned;
     t.R = R;
     t.RT = sh.RT;
     t.KC = K / 128;
@@ -281,15 +293,17 @@ int gemm_mr_part_blocks(const MrPlan& m) { return m.S > 1 ? (m.T * 16 + kRedCols
 hipError_t launch_gemm_mr(const void* X, size_t xplane, const void* Wp, const MrPlan& m, const Epi& ep,
                           hipStream_t st) {
   if (m.R < 1 || m.R > kMaxRows || m.T < 1 || m.KC < 1 || m.gr < 1 || m.T % m.gr || m.n_cg < 1 ||
-      m.n_cg > m.T / m.gr || m.S < 1 || m.S > 4 * m.KC || m.RT < 1 || m.chunks != (m.R + 16 * m.RT - 1) / (16 * m.RT) ||
-      ep.row0 != 0)
+      m.n_cg > m.T / m.gr || m.S < 1 || m.S > (m.any ? 2 : 4) * m.KC || m.RT < 1 ||
+      m.chunks != (m.R + 16 * m.RT - 1) / (16 * m.RT) || ep.row0 != 0)
     return hipErrorInvalidValue;
   // every group must fit the workgroup's column tiles
   const int U = m.T / m.gr;
   if ((U + m.n_cg - 1) / m.n_cg * m.gr > m.CT) return hipErrorInvalidValue;
   if (m.S > 1 && (!ep.kpart || (size_t)m.S * m.R * m.T * 16 > kGemmPartFloats)) return hipErrorInvalidValue;
+  if (!m.any && (((uintptr_t)X | (uintptr_t)Wp | (xplane * sizeof(bf16_t))) & 15)) return hipErrorInvalidValue;
   hipError_t e = hipErrorInvalidValue;
-  switch (m.RT) {
+  if (m.any) e = launch_mr_any(X, xplane, Wp, m, ep, st);
+  else switch (m.RT) {
     case 2: e = launch_mr_rt2(X, xplane, Wp, m, ep, st); break;
     case 4: e = launch_mr_rt4(X, xplane, Wp, m, ep, st); break;
     case 6: e = launch_mr_rt6(X, xplane, Wp, m, ep, st); break;

@@ -386,15 +386,16 @@ static int device_cus() {
 // One projection Y[R][N] = X[R][K] W^T with epilogue ep: the many-row kernel
 // (gemm_mr.h) for bf16 where its plan takes the shape (from 10, 17, 25, 33 or
 // 65 rows, by the matrix), else the weight-streaming kernel.  The many-row
-// kernel's loads go straight to LDS, 16 bytes a lane, and need operands
-// aligned to that.  *part_blocks (if not null) gets the number of per-row
-// argmax key slots the launch writes (EPI_ARGMAX).  split_k = false keeps K
-// in one workgroup (callers without split-K scratch).
+// kernel's loads go straight to LDS, 16 bytes a lane, and need operands aligned
+// to that; others have a plan of their own.  *part_blocks (if not null) gets the
+// number of per-row argmax key slots the launch writes (EPI_ARGMAX).  split_k =
+// false keeps K in one workgroup (callers without split-K scratch).
 static hipError_t run_gemm(int dtype, int R, int N, int K, const void* X, size_t xplane, const void* W, const Epi& ep,
                            hipStream_t st, int* part_blocks = nullptr, bool split_k = true) {
-  if (dtype == JF_BF16 && ep.row0 == 0 && ((uintptr_t)X & 15) == 0 && ((uintptr_t)W & 15) == 0) {
+  if (dtype == JF_BF16 && ep.row0 == 0) {
+    const bool aligned = (((uintptr_t)X | (uintptr_t)W | (xplane * 2)) & 15) == 0;
     MrPlan mp{};
-    if (gemm_mr_plan(mp, R, N, K, ep.kind, device_cus(), split_k ? 64 : 1)) {
+    if (gemm_mr_plan(mp, R, N, K, ep.kind, device_cus(), split_k ? 64 : 1, aligned)) {
       if (part_blocks) *part_blocks = gemm_mr_part_blocks(mp);
       return launch_gemm_mr(X, xplane, W, mp, ep, st);
     }

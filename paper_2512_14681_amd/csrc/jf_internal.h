@@ -116,18 +116,21 @@ struct MrPlan {
   int n_cg;         // column groups
   int S;            // K splits (partials in Epi::kpart, S x R x N floats)
   int chunks;       // row chunks
+  int any;          // 1: operands of any alignment (else both 16-byte aligned)
 };
 // false if the shape is not for this kernel; max_splits 1: no split-K
-// scratch
-bool gemm_mr_plan(MrPlan& m, int R, int N, int K, int epi_kind, int n_cus, int max_splits);
+// scratch; aligned: both operands start on 16-byte boundaries
+bool gemm_mr_plan(MrPlan& m, int R, int N, int K, int epi_kind, int n_cus, int max_splits, bool aligned);
 // per-block argmax slots (EPI_ARGMAX) the plan's epilogue writes
 int gemm_mr_part_blocks(const MrPlan& m);
 hipError_t launch_gemm_mr(const void* X, size_t xplane, const void* Wp, const MrPlan& m, const Epi& ep,
                           hipStream_t stream);
-// the main kernel of one row-tile count (gemm_mr_rt*.hip)
+// the main kernel of one row-tile count (gemm_mr_rt*.hip), and the one for
+// operands of any alignment (gemm_mr_any.hip)
 typedef hipError_t MrLaunch(const void* X, size_t xplane, const void* Wp, const MrPlan& m, const Epi& ep,
                             hipStream_t stream);
-MrLaunch launch_mr_rt2, launch_mr_rt4, launch_mr_rt6, launch_mr_rt8, launch_mr_rt10, launch_mr_rt12, launch_mr_rt16;
+MrLaunch launch_mr_rt2, launch_mr_rt4, launch_mr_rt6, launch_mr_rt8, launch_mr_rt10, launch_mr_rt12, launch_mr_rt16,
+    launch_mr_any;
 
 // Packs W[rows][cols] (row-major) into the kernels' block layout, reading
 // source row rowmap[i] (or i if rowmap is null) from one of up to 4 source

@@ -116,6 +116,44 @@ def test_step_logits_ragged_many_rows(env, n):
     assert ((g == zo.argmax(1)) | (gaps(zo) < GAP_EXEMPT)).all()
 
 
+@pytest.mark.parametrize("n", [49, 90])
+def test_step_logits_with_buffers_off_a_16_byte_boundary(env, n):
+    """Packed weights and workspace 8 bytes past a 16-byte boundary (the
+    workspace holds 64-bit words): every projection's epilogue on the kernel
+    for such operands, with and without split K."""
+    import ctypes
+    import torch
+    from paper_2512_14681_amd import decode, jf
+
+    class Shifted(jf.Model):
+        def __init__(self, shape, weights, max_rows, max_ctx):
+            self.torch, self.shape, self.stream, self.V = torch, dict(shape), None, shape["vocab"]
+            self.cfg = jf.config(shape, max_rows, max_ctx)
+            self.raw = [torch.empty(b + 8, dtype=torch.uint8, device="cuda") for b in jf.query_sizes(self.cfg)]
+            assert all(t.data_ptr() % 16 == 0 for t in self.raw)
+            self.packed, self.kv, self.ws = self.raw[0][8:], self.raw[1][:-8], self.raw[2][8:]
+            dev = [torch.from_numpy(np.ascontiguousarray(weights[k]).view(np.int16)).to("cuda")
+                   for k in jf.weight_names(shape)]
+            ptrs = (ctypes.c_void_p * len(dev))(*[t.data_ptr() for t in dev])
+            self.h = ctypes.c_void_p()
+            jf.check(jf.lib().jf_model_load(ctypes.byref(self.cfg), ptrs, len(dev), jf._ptr(self.packed),
+                                            jf._ptr(self.kv), jf._ptr(self.ws), jf._stream(), ctypes.byref(self.h)))
+
+    dec = decode.Decoder(Shifted(SHAPE, env["w"], 96, 512))
+    p = dec.prefill(env["prompt"])
+    draft = [p] + [ojac.pad_id(4, 80 + i, SHAPE["vocab"]) for i in range(1, n)]
+    d_draft = torch.tensor(draft, dtype=torch.int32, device="cuda")
+    d_next = torch.zeros(n, dtype=torch.int32, device="cuda")
+    d_log = torch.empty((n, SHAPE["vocab"]), dtype=torch.float32, device="cuda")
+    dec.m.jf_jacobi_step(d_draft, n, 1, 4, dec.d_argmax, dec.d_result, d_next, d_log)
+    z = d_log.cpu().numpy()
+    g = dec.d_argmax[:n].cpu().numpy()
+    zo = teacher_forced(env, list(env["prompt"]) + draft)[80:80 + n]
+    err = np.abs(z - zo).max()
+    assert err < LOGIT_TOL, err
+    assert ((g == zo.argmax(1)) | (gaps(zo) < GAP_EXEMPT)).all()
+
+
 @pytest.mark.parametrize("n,mode", [(16, "window"), (8, "block")])
 def test_decode_matches_oracle_argmax(env, n, mode):
     dec = env["dec"]

@@ -85,6 +85,70 @@ def top2(z):
     return s[:, -1] - s[:, -2]
 
 
+def split_planes(x):
+    """fp32 values as activation planes: the bits of hi = bf16(x) and of lo =
+    bf16(x - hi), and the value hi + lo they stand for (float64)."""
+    hi = bf16_bits(x)
+    lo = bf16_bits(x.astype(np.float64) - bf16_bits_to_float(hi))
+    return hi, lo, bf16_bits_to_float(hi) + bf16_bits_to_float(lo)
+
+
+def at_offset(a, off):
+    """A device copy of `a` that starts `off` bytes past a 256-byte boundary."""
+    torch = _torch()
+    raw = np.ascontiguousarray(a).view(np.uint8).reshape(-1)
+    buf = torch.empty(raw.size + 256, dtype=torch.uint8, device="cuda")
+    base = (-buf.data_ptr()) % 256 + off
+    view = buf[base:base + raw.size]
+    view.copy_(torch.from_numpy(raw))
+    return view
+
+
+def run_lm_head_planes(hi, lo, w, draft=None, x_off=0, w_off=0):
+    """(argmax, logits) of the bf16 LM head on the rows hi + lo; the two
+    operands start x_off and w_off bytes past a 256-byte boundary."""
+    torch = _torch()
+    from paper_2512_14681_amd import jf
+    L, (R, d), V = jf.lib(), hi.shape, w.shape[0]
+    d_w = to_dev(w)
+    d_wp = at_offset(np.zeros(V * d, np.uint16), w_off)
+    st = jf._stream()
+    jf.check(L.jf_pack_matrix(V, d, jf.JF_BF16, jf._ptr(d_w), jf._ptr(d_wp), st))
+    d_x = at_offset(np.stack([jf.act_layout(hi), jf.act_layout(lo)]), x_off)
+    d_g = torch.zeros(R, dtype=torch.int32, device="cuda")
+    d_log = torch.full((R, V), float("nan"), dtype=torch.float32, device="cuda")
+    d_ws = torch.empty(L.jf_lm_head_ws_bytes(R, V), dtype=torch.uint8, device="cuda")
+    jf.check(L.jf_lm_head_accept(R, d, V, jf.JF_BF16, jf._ptr(d_x), jf._ptr(d_wp), None, jf._ptr(d_g), None,
+                                 jf._ptr(d_log), jf._ptr(d_ws), st))
+    torch.cuda.synchronize()
+    return d_g.cpu().numpy(), d_log.cpu().numpy()
+
+
+def check_planes(g, logits, z):
+    """fp32 sums of K products of two 16-bit planes against the product in 64
+    bits: K / 32 roundings of 2^-24 a chain, relative to the result below
+    1e-6 in the 2-norm (dropping the lo plane: 1e-3); the tokens agree but for
+    near-ties."""
+    assert np.isfinite(logits).all()
+    assert np.linalg.norm(logits - z) < 2e-6 * np.linalg.norm(z)
+    assert np.abs(logits - z).max() < 1e-4
+    assert ((g == np.argmax(z, axis=1)) | (top2(z) < 1e-4)).all()
+
+
+@pytest.mark.parametrize("R,x_off,w_off", [(1, 2, 2), (24, 8, 2), (32, 2, 0), (33, 0, 2), (64, 8, 0), (65, 0, 8),
+                                           (96, 8, 8), (100, 4, 2), (177, 2, 14), (300, 8, 8), (512, 6, 2)])
+def test_lm_head_operands_off_a_16_byte_boundary(R, x_off, w_off):
+    """Operands that start anywhere their elements may: the kernel whose loads
+    go through registers (from 33 rows), in one to four chunks with ragged
+    last row tiles, and the weight-streaming kernel below."""
+    d, V = 1024, 32784
+    x = jf_inputs.normal(9, 1, R * d, dtype="f32").reshape(R, d)
+    w = jf_inputs.normal(9, 2, V * d, std=0.02, dtype="bf16").reshape(V, d)
+    hi, lo, xv = split_planes(x)
+    g, logits = run_lm_head_planes(hi, lo, w, x_off=x_off, w_off=w_off)
+    check_planes(g, logits, xv @ bf16_bits_to_float(w).T)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("R", [1, 16, 17, 64, 200])
 def test_lm_head_small(dtype, R):

@@ -26,15 +26,15 @@ CUS = 256
 
 
 class MrPlan(ctypes.Structure):
-    _fields_ = [(k, I) for k in ("R", "RT", "CT", "KC", "P", "T", "gr", "n_cg", "S", "chunks")]
+    _fields_ = [(k, I) for k in ("R", "RT", "CT", "KC", "P", "T", "gr", "n_cg", "S", "chunks", "any")]
 
 
-def mr_plan(L, R, N, K, epi, splits=64):
+def mr_plan(L, R, N, K, epi, splits=64, aligned=True):
     """The many-row GEMM's plan of [R][K] x [N][K]^T, or None: another kernel runs it."""
-    f = L._ZN2jf12gemm_mr_planERNS_6MrPlanEiiiiii
-    f.restype, f.argtypes = ctypes.c_bool, [ctypes.POINTER(MrPlan), I, I, I, I, I, I]
+    f = L._ZN2jf12gemm_mr_planERNS_6MrPlanEiiiiiib
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.POINTER(MrPlan), I, I, I, I, I, I, ctypes.c_bool]
     m = MrPlan()
-    return m if f(ctypes.byref(m), R, N, K, epi, CUS, splits) else None
+    return m if f(ctypes.byref(m), R, N, K, epi, CUS, splits, aligned) else None
 
 
 @pytest.mark.parametrize("R,N,K", [(320, 4608, 2560), (448, 4608, 2560), (160, 6144, 2560), (320, 6144, 2560),
@@ -104,6 +104,21 @@ def test_lm_head_without_split_k_scratch(L, R, N, K, here):
     assert m is None or m.S == 1
     if K >= 8192 and R >= 25:
         assert mr_plan(L, R, N, K, EPI_ARGMAX) is not None
+
+
+def test_operands_off_a_16_byte_boundary(L):
+    """They have the many-row kernel too, from 33 rows, in the chunks that are
+    built for them and for the same matrices."""
+    for N, K, epi in ((37888, 3584, EPI_SWIGLU), (3584, 18944, EPI_RESID), (4608, 3584, EPI_QKV),
+                      (3584, 3584, EPI_RESID), (8192, 3584, EPI_ARGMAX), (1024, 1024, EPI_RESID)):
+        for R in list(range(1, 129)) + [192, 320, 512]:
+            m, a = mr_plan(L, R, N, K, epi, aligned=False), mr_plan(L, R, N, K, epi)
+            assert a is None or a.any == 0
+            if R < 33:
+                assert m is None
+            else:
+                assert (m is None) == (a is None)
+                assert m is None or (m.any == 1 and m.RT in (4, 6, 8) and m.CT in ((4, 8, 12) if m.RT == 6 else (2, 4, 6, 8, 10, 12)))
 
 
 # ---- trajectory selection ---------------------------------------------------------
