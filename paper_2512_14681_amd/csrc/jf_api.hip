@@ -383,29 +383,36 @@ static int device_cus() {
   return cus > 0 ? cus : 256;
 }
 
-// One projection Y[R][N] = X[R][K] W^T with epilogue ep: the many-row kernel
-// (gemm_mr.h) for bf16 where its plan takes the shape (from 10, 17, 25, 33 or
-// 65 rows, by the matrix), else the weight-streaming kernel.  The many-row
-// kernel's loads go straight to LDS, 16 bytes a lane, and need operands aligned
-// to that; others have a plan of their own.  *part_blocks (if not null) gets the
-// number of per-row argmax key slots the launch writes (EPI_ARGMAX).  split_k =
-// false keeps K in one workgroup (callers without split-K scratch).
-static hipError_t run_gemm(int dtype, int R, int N, int K, const void* X, size_t xplane, const void* W, const Epi& ep,
-                           hipStream_t st, int* part_blocks = nullptr, bool split_k = true) {
-  if (dtype == JF_BF16 && ep.row0 == 0) {
-    const bool aligned = (((uintptr_t)X | (uintptr_t)W | (xplane * 2)) & 15) == 0;
-    MrPlan mp{};
-    if (gemm_mr_plan(mp, R, N, K, ep.kind, device_cus(), split_k ? 64 : 1, aligned)) {
-      if (part_blocks) *part_blocks = gemm_mr_part_blocks(mp);
-      return launch_gemm_mr(X, xplane, W, mp, ep, st);
-    }
-  }
-  GemmShape gs{R, N, K, 1, 1, 1};
-  gemm_plan(gs, ep.kind);
-  if (!split_k) gs.S = 1;
-  else gemm_tail_split(gs, device_cus());
-  if (part_blocks) *part_blocks = (int)gemm_blocks(gs);
-  return launch_gemm(dtype, X, xplane, W, gs, ep, st);
+// A projection Y[R][N] = X[R][K] W^T with an epilogue of kind epi_kind: the
+// many-row kernel (gemm_mr.h) for bf16 where its plan takes the shape (from 10,
+// 17, 25, 33 or 65 rows, by the matrix), else the weight-streaming kernel.  The
+// many-row kernel's loads go straight to LDS, 16 bytes a lane, and need operands
+// aligned to that; others have a plan of their own.  row0: first row of X read
+// (Epi::row0).  split_k = false keeps K in one workgroup (callers without split-K
+// scratch).
+struct GemmRun {
+  bool many;
+  MrPlan mp;
+  GemmShape gs;
+  // per-row argmax key slots a launch writes (EPI_ARGMAX)
+  int part_blocks() const { return many ? gemm_mr_part_blocks(mp) : (int)gemm_blocks(gs); }
+};
+static GemmRun plan_gemm(int dtype, int R, int N, int K, int epi_kind, const void* X, size_t xplane, const void* W,
+                         int row0 = 0, bool split_k = true) {
+  GemmRun g{};
+  const bool aligned = (((uintptr_t)X | (uintptr_t)W | (xplane * 2)) & 15) == 0;
+  g.many = dtype == JF_BF16 && row0 == 0 &&
+           gemm_mr_plan(g.mp, R, N, K, epi_kind, device_cus(), split_k ? 64 : 1, aligned);
+  if (g.many) return g;
+  g.gs = GemmShape{R, N, K, 1, 1, 1};
+  gemm_plan(g.gs, epi_kind);
+  if (!split_k) g.gs.S = 1;
+  else gemm_tail_split(g.gs, device_cus());
+  return g;
+}
+static hipError_t run_gemm(const GemmRun& g, int dtype, const void* X, size_t xplane, const void* W, const Epi& ep,
+                           hipStream_t st) {
+  return g.many ? launch_gemm_mr(X, xplane, W, g.mp, ep, st) : launch_gemm(dtype, X, xplane, W, g.gs, ep, st);
 }
 
 // ---- forward pass of one step ---------------------------------------------------------
@@ -467,6 +474,14 @@ static jf_status forward(jf_model* m, const int32_t* d_tokens, int R, const SegA
     attn_block_plan(sa);
     fused = sa.G * sa.qtiles <= kAttnBlockMaxGT && sa.splits <= kAttnMaxSplits && sa.kc_o <= 32;
   }
+  // The layers' projections are planned once: the plan depends on the shapes
+  // and on the operands' alignment, the same in every layer (a plan of the
+  // many-row kernel takes about as long to find as a launch to enqueue).
+  char* l0 = m->layer(0);
+  const GemmRun g_qkv = plan_gemm(dt, R, L.qkv_rows, d, EPI_QKV, xn, pl_d, l0 + L.l_qkv);
+  const GemmRun g_o = plan_gemm(dt, R, d, Hhd, EPI_RESID, m->ws + L.w_attn, pl_h, l0 + L.l_o);
+  const GemmRun g_gu = plan_gemm(dt, R, 2 * F, d, EPI_SWIGLU, xn, pl_d, l0 + L.l_gu);
+  const GemmRun g_down = plan_gemm(dt, R, d, F, EPI_RESID, m->ws + L.w_act, pl_f, l0 + L.l_down);
   for (int l = 0; l < c.n_layers; ++l) {
     char* lp = m->layer(l);
     if (fused) {
@@ -497,7 +512,7 @@ static jf_status forward(jf_model* m, const int32_t* d_tokens, int R, const SegA
       ep.pos = pos; ep.state = state; ep.rope_cos = m->at<float>(L.w_cos); ep.rope_sin = m->at<float>(L.w_sin);
       ep.H = H; ep.G = G; ep.hd = hd; ep.max_ctx = c.max_ctx; ep.flags = m->flags();
       PROF(JF_KERNEL_QKV);
-      HIP_TRY(run_gemm(dt, R, m->L.qkv_rows, d, xn, pl_d, lp + L.l_qkv, ep, st));
+      HIP_TRY(run_gemm(g_qkv, dt, xn, pl_d, lp + L.l_qkv, ep, st));
       PROF(JF_KERNEL_QKV);
     }
     // a4: attention
@@ -520,7 +535,7 @@ static jf_status forward(jf_model* m, const int32_t* d_tokens, int R, const SegA
       ep.kind = EPI_RESID; ep.R = R; ep.f32 = h; ep.ldf = d;
       norm_out(ep, (const float*)(lp + L.l_fn), ss_f, ss_a);
       PROF(JF_KERNEL_O);
-      HIP_TRY(run_gemm(dt, R, d, Hhd, m->ws + L.w_attn, pl_h, lp + L.l_o, ep, st));
+      HIP_TRY(run_gemm(g_o, dt, m->ws + L.w_attn, pl_h, lp + L.l_o, ep, st));
       PROF(JF_KERNEL_O);
     }
     // a6: FFN RMSNorm (folded), gate/up + SwiGLU, down + residual
@@ -529,7 +544,7 @@ static jf_status forward(jf_model* m, const int32_t* d_tokens, int R, const SegA
       ep.kind = EPI_SWIGLU; ep.R = R; ep.act = m->ws + L.w_act; ep.act_k = F; ep.act_plane = pl_f;
       norm_in(ep, ss_f);
       PROF(JF_KERNEL_GATEUP);
-      HIP_TRY(run_gemm(dt, R, 2 * F, d, xn, pl_d, lp + L.l_gu, ep, st));
+      HIP_TRY(run_gemm(g_gu, dt, xn, pl_d, lp + L.l_gu, ep, st));
       PROF(JF_KERNEL_GATEUP);
     }
     // down projection + residual, writing the next RMSNorm's input (the next
@@ -542,7 +557,7 @@ static jf_status forward(jf_model* m, const int32_t* d_tokens, int R, const SegA
       else if (lm != 0)
         norm_out(ep, (const float*)(m->packed + L.p_final), ss_a, ss_f);
       PROF(JF_KERNEL_DOWN);
-      HIP_TRY(run_gemm(dt, R, d, F, m->ws + L.w_act, pl_f, lp + L.l_down, ep, st));
+      HIP_TRY(run_gemm(g_down, dt, m->ws + L.w_act, pl_f, lp + L.l_down, ep, st));
       PROF(JF_KERNEL_DOWN);
     }
   }
@@ -556,14 +571,14 @@ static jf_status forward(jf_model* m, const int32_t* d_tokens, int R, const SegA
   ep.row0 = lm == 2 ? R - 1 : 0;
   norm_in(ep, ss_a);
   PROF(JF_KERNEL_LMHEAD);
-  int part_blocks = 0;
-  HIP_TRY(run_gemm(dt, Rl, c.vocab, d, xn, pl_d, m->packed + L.p_lm, ep, st, &part_blocks));
+  const GemmRun g_lm = plan_gemm(dt, Rl, c.vocab, d, EPI_ARGMAX, xn, pl_d, m->packed + L.p_lm, ep.row0);
+  HIP_TRY(run_gemm(g_lm, dt, xn, pl_d, m->packed + L.p_lm, ep, st));
   PROF(JF_KERNEL_LMHEAD);
   if (lm_parts) {
-    *lm_parts = part_blocks;
+    *lm_parts = g_lm.part_blocks();
     return JF_OK;
   }
-  HIP_TRY(launch_argmax_reduce(ep.part, part_blocks, L.Rp, Rl, d_g, st));
+  HIP_TRY(launch_argmax_reduce(ep.part, g_lm.part_blocks(), L.Rp, Rl, d_g, st));
   return JF_OK;
 }
 
@@ -844,10 +859,11 @@ extern "C" jf_status jf_lm_head_accept(int32_t R, int32_t d, int32_t V, int32_t 
   Epi ep{};
   ep.kind = EPI_ARGMAX; ep.R = R; ep.part = (uint64_t*)d_ws; ep.part_stride = R;
   ep.logits = d_logits; ep.ldl = V;
-  int part_blocks = 0;
   // no split-K scratch in the component call
-  HIP_TRY(run_gemm(dtype, R, V, d, d_x, (size_t)(R + 15) / 16 * 16 * d, d_w_packed, ep, st, &part_blocks, false));
-  HIP_TRY(launch_argmax_reduce(ep.part, part_blocks, R, R, d_argmax, st));
+  const size_t plane = (size_t)(R + 15) / 16 * 16 * d;
+  const GemmRun g = plan_gemm(dtype, R, V, d, EPI_ARGMAX, d_x, plane, d_w_packed, 0, false);
+  HIP_TRY(run_gemm(g, dtype, d_x, plane, d_w_packed, ep, st));
+  HIP_TRY(launch_argmax_reduce(ep.part, g.part_blocks(), R, R, d_argmax, st));
   if (d_draft) {
     int32_t* zero = (int32_t*)((char*)d_ws + (size_t)(V / 16) * R * 8);
     HIP_TRY(launch_set_int(zero, 0, st));
