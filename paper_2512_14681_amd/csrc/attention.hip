@@ -665,11 +665,14 @@ __global__ void __launch_bounds__(512, 1) k_attn_lds(AttnArgs a) {
 // Launch shape: key splits such that each of a block's 4 waves gets at most
 // kAttnChunksPerWave 32-key chunks (one memory round trip), at most
 // kAttnMaxSplits splits, and at most kAttnMaxPages - 2 pages per split.
-// Two query tiles per block from this many (query tiles x keys) on: measured
-// on the attention workloads (28 q / 4 kv heads of 128), two tiles won at
-// 57k and more (P = 8192, n = 16: -17%; P = 2048, n = 64: -15%) and lost at
-// 29k (P = 2048, n = 32: +5%), where the one-chunk-in-flight loop costs more
-// than the halved key traffic saves.
+// Two query tiles per block from this many (query tiles x keys) on, where the
+// one-chunk-in-flight loop no longer costs more than the halved key traffic
+// saves.  The line was drawn at 28 q / 4 kv heads of 128 (won at 57k and more,
+// lost at 29k), before that head_dim had the LDS-shared form, and carried over to
+// 32 and 64.  At 64 the forms cross near 250k / KV heads, so it is early for 2 KV
+// heads and late for 8 (us, one tile -> two: 2 KV heads, 32 rows after 4000 / 8000
+// keys, 64k / 128k, 12.4 -> 13.6 / 18.2 -> 15.9; 8 KV heads, 64 / 96 rows after
+// 4000, 33k / 49k, 17.2 -> 14.7 / 21.9 -> 18.6, which run one tile).
 constexpr long kAttnQt2Work = 50000;
 
 // The LDS-shared form: query groups of up to 8 tiles (balanced), and key
@@ -767,9 +770,10 @@ static hipError_t launch_checked(int dtype, const AttnArgs& a, hipStream_t st) {
 }
 
 // The two-tile form (bf16): its key splits are halved while the grid has
-// more than kAttnQt2Blocks blocks.  Measured on the attention workloads at
-// P = 8192 (32 splits from the one-tile plan): the wider combine of many
-// splits costs more than the extra blocks gain once the grid is that large.
+// more than kAttnQt2Blocks blocks.  Measured at 28 q / 4 kv heads of 128 after
+// 8192 keys (32 splits from the one-tile plan) and carried over with the line
+// above: the wider combine of many splits costs more than the extra blocks gain
+// once the grid is that large.
 // Best were 16 splits at n = 16 (256 blocks, -9%) and n = 32 (448 blocks,
 // -29%), 8 at n = 64 (448 blocks, -41%); 256 or 512 as the bound each lost
 // one of them.

@@ -366,14 +366,15 @@ static bool plan_residual(GemmShape& s) {
 // more (three or more chunks).  The rule above over-splits the long-K down
 // projection and, once chunked, keeps too many waves per chunk: the C chunk
 // blocks of a unit already multiply the waves in flight by C.
-// Many of these rows run on the many-row kernel now (mr_takes in gemm_mr.hip);
-// what is left here is fp32 models, operands that are not 16-byte aligned, and
-// O and other small matrices up to 64 rows.
+// The many-row kernel has taken most of the bf16 ones over (mr_takes in
+// gemm_mr.hip).  What runs here is fp32 models (one 7B layer and the LM head with
+// these plans, against the rule above: 48 rows 1081 / 1180 us, 96 rows 1547 /
+// 1599, 192 rows 2728 / 2940; the gains below are bf16 steps') and, in bf16, O up
+// to 64 rows, down and the LM head up to 24 and, by the rule, QKV up to 32.
 struct MeasuredPlan { int epi, N, K, NT, WK, S, D; };
 static const MeasuredPlan kPlans32[] = {
     {EPI_RESID, 3584, 18944, 4, 4, 4, 0},    // down: -107 us per n = 32 step vs the rule
     {EPI_RESID, 3584, 3584, 2, 8, 2, 0},     // O: -29 us
-    {EPI_SWIGLU, 37888, 3584, 4, 4, 1, 0},   // gate/up: -32 us
     {EPI_ARGMAX, 152064, 3584, 4, 4, 1, 0},  // LM head: -16 us
 };
 static const MeasuredPlan kPlans64[] = {     // per 32-row chunk, C = 2
