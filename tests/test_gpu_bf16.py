@@ -71,9 +71,9 @@ def test_step_logits(env):
 
 @pytest.mark.parametrize("n", [80, 96])
 def test_step_logits_column_slice_rows(env, n):
-    """Steps of 65 to 96 rows run every projection on the column-slice GEMM
-    (QKV and O with split K and the ordered reduction): all rows' logits
-    against the teacher-forced oracle."""
+    """Steps of 65 to 96 rows run every projection on the many-row GEMM (QKV and
+    O with split K and the ordered reduction): all rows' logits against the
+    teacher-forced oracle."""
     import torch
     from paper_2512_14681_amd import decode, jf
     model = jf.Model(SHAPE, env["w"], max_rows=96, max_ctx=512)
@@ -92,7 +92,7 @@ def test_step_logits_column_slice_rows(env, n):
     assert ((g == zo.argmax(1)) | (gaps(zo) < GAP_EXEMPT)).all()
 
 
-@pytest.mark.parametrize("n", [17, 49, 65, 161, 257])
+@pytest.mark.parametrize("n", [17, 32, 49, 65, 161, 257])
 def test_step_logits_ragged_many_rows(env, n):
     """One row past a row-tile boundary of the many-row GEMM: the split-K
     reduction, the RoPE / cache-write, SwiGLU and residual epilogues with a
@@ -114,6 +114,32 @@ def test_step_logits_ragged_many_rows(env, n):
     err = np.abs(z - zo).max()
     assert err < LOGIT_TOL, err
     assert ((g == zo.argmax(1)) | (gaps(zo) < GAP_EXEMPT)).all()
+
+
+@pytest.mark.parametrize("n", [10, 13, 15, 16])
+def test_step_logits_few_rows_of_a_wide_ffn(n):
+    """10 to 16 rows of a decoder whose gate/up projection (2560 column tiles)
+    is on the many-row GEMM there, ragged and full."""
+    import torch
+    from paper_2512_14681_amd import decode, jf
+    shape = dict(n_layers=1, d_model=256, n_heads=4, n_kv_heads=2, head_dim=64, d_ffn=20480, vocab=1024,
+                 rope_base=10000.0, rms_eps=1e-6, dtype="bf16")
+    w = jf_inputs.model_weights(shape, seed=8)
+    prompt = jf_inputs.prompt(9, 20, shape["vocab"])
+    dec = decode.Decoder(jf.Model(shape, w, max_rows=64, max_ctx=128))
+    p = dec.prefill(prompt)
+    draft = [p] + [ojac.pad_id(4, 20 + i, shape["vocab"]) for i in range(1, n)]
+    d_draft = torch.tensor(draft, dtype=torch.int32, device="cuda")
+    d_next = torch.zeros(n, dtype=torch.int32, device="cuda")
+    d_log = torch.empty((n, shape["vocab"]), dtype=torch.float32, device="cuda")
+    dec.m.jf_jacobi_step(d_draft, n, 1, 4, dec.d_argmax, dec.d_result, d_next, d_log)
+    z = d_log.cpu().numpy()
+    m = DecoderOracle(shape, w)
+    T = 20 + n
+    zo, _ = m.forward(np.asarray(list(prompt) + draft), np.arange(T), np.tri(T, dtype=bool))
+    zo = zo[20:]
+    assert np.abs(z - zo).max() < LOGIT_TOL
+    assert ((dec.d_argmax[:n].cpu().numpy() == zo.argmax(1)) | (gaps(zo) < GAP_EXEMPT)).all()
 
 
 @pytest.mark.parametrize("n", [49, 90])

@@ -20,6 +20,7 @@ import pytest
 import jf_inputs
 from oracle.model import DecoderOracle
 from oracle.numerics import bf16_bits_to_float, round_bf16
+from test_plans_cpu import ANY_ALIGNMENT_BLOCKS, MANY_ROW_BLOCKS
 
 pytestmark = pytest.mark.gpu
 
@@ -135,6 +136,41 @@ def check_planes(g, logits, z):
     assert ((g == np.argmax(z, axis=1)) | (top2(z) < 1e-4)).all()
 
 
+def lm_head_case(seed, R, V, d):
+    """(hi, lo, w, product in 64 bits) of N(0, 1) rows in two planes and
+    N(0, 0.02) bf16 weights."""
+    x = jf_inputs.normal(seed, 1, R * d, dtype="f32").reshape(R, d)
+    w = jf_inputs.normal(seed, 2, V * d, std=0.02, dtype="bf16").reshape(V, d)
+    hi, lo, xv = split_planes(x)
+    return hi, lo, w, xv @ bf16_bits_to_float(w).T
+
+
+@pytest.mark.parametrize("block", sorted(MANY_ROW_BLOCKS), ids=lambda b: f"RT{b[0]}-CT{b[1]}")
+def test_lm_head_every_many_row_block(block):
+    """Every block shape of the many-row kernel that a call without split K
+    reaches, with a ragged last row tile and activations whose lo plane
+    counts: which case runs on which shape is checked on the CPU."""
+    R, V, d = MANY_ROW_BLOCKS[block]
+    hi, lo, w, z = lm_head_case(11, R, V, d)
+    check_planes(*run_lm_head_planes(hi, lo, w), z)
+
+
+@pytest.mark.parametrize("block", sorted(ANY_ALIGNMENT_BLOCKS), ids=lambda b: f"RT{b[0]}-CT{b[1]}")
+def test_lm_head_every_block_for_any_alignment(block):
+    """The same for operands 8 and 2 bytes past a 16-byte boundary."""
+    R, V, d = ANY_ALIGNMENT_BLOCKS[block]
+    hi, lo, w, z = lm_head_case(12, R, V, d)
+    check_planes(*run_lm_head_planes(hi, lo, w, x_off=8, w_off=2), z)
+
+
+@pytest.mark.parametrize("R", [1, 9, 16, 17, 24, 32, 33, 64])
+def test_lm_head_weight_streaming_planes(R):
+    """The weight-streaming kernel (a head of 4096 words): the lo plane counts
+    at one and two row tiles and in chunks."""
+    hi, lo, w, z = lm_head_case(13, R, 4096, 1024)
+    check_planes(*run_lm_head_planes(hi, lo, w), z)
+
+
 @pytest.mark.parametrize("R,x_off,w_off", [(1, 2, 2), (24, 8, 2), (32, 2, 0), (33, 0, 2), (64, 8, 0), (65, 0, 8),
                                            (96, 8, 8), (100, 4, 2), (177, 2, 14), (300, 8, 8), (512, 6, 2)])
 def test_lm_head_operands_off_a_16_byte_boundary(R, x_off, w_off):
@@ -182,12 +218,9 @@ def test_lm_head_acceptance_closed_form():
 
 @pytest.mark.parametrize("R", [25, 32, 48, 80, 96, 128, 144, 192, 256, 384, 512])
 def test_lm_head_column_slice_chunks(R):
-    """A vocabulary wide enough for the column-slice GEMM (2048 tiles of 16
-    columns, K = 1024): 32-, 64-, 96- and 128-row chunks, one to four of
-    them (128 and 256 rows: two and four 64-row chunks; 384 rows: four
-    96-row chunks; 512 rows: four 128-row chunks), with ragged last chunks
-    (25 = 32 - 7, 80 = 96 - 16, 144 = 96 + 48).  bf16 values, plain fp64
-    product and argmax."""
+    """A head of 2048 column tiles, K = 1024, on the many-row GEMM: rows at and
+    between the chunk sizes, in one to three chunks.  bf16 values (the lo plane
+    is zero), plain fp64 product and argmax."""
     d, V = 1024, 32768
     x = jf_inputs.normal(5, 1, R * d, dtype="bf16").reshape(R, d)
     w = jf_inputs.normal(5, 2, V * d, std=0.02, dtype="bf16").reshape(V, d)
@@ -199,11 +232,11 @@ def test_lm_head_column_slice_chunks(R):
 
 @pytest.mark.parametrize("R", [33, 49, 65, 97, 129, 161, 193, 257, 321, 449])
 def test_lm_head_many_rows_ragged(R):
-    """One row past each row-tile count of the many-row GEMM (so the last row
-    tile holds one row, and the last chunk of several may be nearly empty),
-    and an odd number of column tiles (513: uneven column groups, the last
-    tile alone in its packed group).  fp32 sums of 2048 products of order
-    0.02: 1e-3 as above."""
+    """One row past a multiple of the row tile (so the last row tile holds one
+    row), and an odd number of column tiles (513: uneven column groups, the
+    last tile alone in its packed group).  bf16 values (the lo plane is zero);
+    every block shape and the lo plane: test_lm_head_every_many_row_block.
+    fp32 sums of 2048 products of order 0.02: 1e-3 as above."""
     d, V = 2048, 8208
     x = jf_inputs.normal(6, 1, R * d, dtype="bf16").reshape(R, d)
     w = jf_inputs.normal(6, 2, V * d, std=0.02, dtype="bf16").reshape(V, d)

@@ -2,12 +2,15 @@
 functions of libjf (paper_2512_14681_amd/csrc/jf_internal.h), called here by
 their C++ names, without a GPU."""
 import ctypes
+import glob
 import os
+import re
 
 import pytest
 
 from paper_2512_14681_amd import jf
 
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_14681_amd", "csrc")
 I = ctypes.c_int
 (SEL_GENERAL, SEL_MULTI_5, SEL_MULTI_8, SEL_MULTI_17, SEL_WIDE_16, SEL_WIDE_32_1, SEL_WIDE_32_3,
  SEL_WIDE_32_4) = range(8)
@@ -35,6 +38,57 @@ def mr_plan(L, R, N, K, epi, splits=64, aligned=True):
     f.restype, f.argtypes = ctypes.c_bool, [ctypes.POINTER(MrPlan), I, I, I, I, I, I, ctypes.c_bool]
     m = MrPlan()
     return m if f(ctypes.byref(m), R, N, K, epi, CUS, splits, aligned) else None
+
+
+# An LM head (rows, words, width; no split-K scratch) for every block shape of
+# the many-row kernel that such a call reaches, {(RT, CT): (R, V, d)}: RT row
+# tiles by CT column tiles.  The last row tile of the last chunk is there and
+# ragged; 16 stages, more than any ring is deep, but where V is small.
+MANY_ROW_BLOCKS = {
+    (2, 8): (17, 32768, 512), (2, 12): (17, 32784, 512), (4, 2): (246, 1600, 512), (4, 4): (113, 4112, 512),
+    (4, 6): (241, 4112, 512), (4, 8): (241, 6400, 512), (4, 10): (241, 8208, 512), (4, 12): (113, 22400, 512),
+    (6, 4): (177, 2560, 512), (6, 8): (369, 4112, 512), (6, 12): (177, 16400, 512), (8, 2): (497, 1024, 512),
+    (8, 4): (497, 2560, 512), (8, 6): (497, 4112, 512), (8, 8): (497, 6400, 512), (8, 10): (497, 8208, 512),
+    (8, 12): (497, 11200, 512), (10, 4): (305, 4112, 512), (10, 8): (305, 8208, 512), (10, 12): (305, 16400, 512),
+    (10, 16): (305, 24592, 512), (12, 2): (369, 1344, 128), (12, 4): (369, 7232, 256), (12, 6): (369, 8208, 512),
+    (12, 8): (369, 12304, 512), (12, 10): (369, 16400, 512), (12, 12): (369, 22400, 512), (16, 2): (497, 3136, 128),
+    (16, 4): (497, 6208, 128), (16, 6): (497, 12288, 512), (16, 8): (497, 12304, 512), (16, 10): (497, 16400, 512)}
+
+# The same for operands off a 16-byte boundary.
+ANY_ALIGNMENT_BLOCKS = {
+    (4, 2): (246, 1600, 512), (4, 4): (113, 4112, 640), (4, 6): (241, 4112, 512), (4, 8): (49, 27200, 640),
+    (4, 10): (113, 16400, 512), (4, 12): (49, 40976, 512), (6, 4): (369, 1600, 512), (6, 8): (369, 4112, 512),
+    (6, 12): (369, 8208, 512), (8, 2): (497, 1024, 512), (8, 4): (497, 2560, 512), (8, 6): (497, 4112, 512),
+    (8, 8): (497, 6400, 512), (8, 10): (497, 8208, 512), (8, 12): (497, 11200, 512)}
+
+
+def instantiated_blocks(files):
+    """(RT, CT) of every k_gemm_mr in the sources that match `files`."""
+    out = set()
+    for path in glob.glob(os.path.join(CSRC, files)):
+        with open(path) as f:
+            for mt, nt, wm, wn in re.findall(r"return launch_mr_cfg<(\d+), (\d+), (\d+), (\d+),", f.read()):
+                out.add((int(mt) * int(wm), int(nt) * int(wn)))
+    return out
+
+
+@pytest.mark.parametrize("aligned", [True, False])
+def test_every_block_shape_has_a_case(L, aligned):
+    """The cases run on the block shapes they are listed under, and are all
+    there are, but for the one that only split K reaches: a down projection's
+    at 25 to 32 rows (the 32-row step of the mid-size decoder)."""
+    cases = MANY_ROW_BLOCKS if aligned else ANY_ALIGNMENT_BLOCKS
+    for (rt, ct), (R, V, d) in cases.items():
+        m = mr_plan(L, R, V, d, EPI_ARGMAX, splits=1, aligned=aligned)
+        assert m and (m.RT, m.CT, m.S) == (rt, ct, 1), ((rt, ct), m and (m.RT, m.CT, m.S))
+        last = R - (m.chunks - 1) * 16 * rt
+        assert 16 * (rt - 1) < last < 16 * rt
+    if aligned:
+        down = mr_plan(L, 32, 2048, 8192, EPI_RESID)
+        assert (down.RT, down.CT) == (2, 4) and down.S > 1
+        assert set(cases) | {(2, 4)} == instantiated_blocks("gemm_mr_rt*.hip")
+    else:
+        assert set(cases) == instantiated_blocks("gemm_mr_any.hip")
 
 
 @pytest.mark.parametrize("R,N,K", [(320, 4608, 2560), (448, 4608, 2560), (160, 6144, 2560), (320, 6144, 2560),
@@ -72,6 +126,14 @@ def test_33_to_64_rows_by_what_the_streaming_kernel_fills(L, N, K, epi, here):
     weight-streaming kernel's workgroups stay on it up to 26M elements."""
     for R in (33, 48, 64):
         assert (mr_plan(L, R, N, K, epi) is not None) == here
+
+
+def test_the_few_row_step_of_the_wide_decoder(L):
+    """The decoder of the GPU parity test at 10 to 16 rows has its gate/up
+    projection here."""
+    for R in (10, 13, 15, 16):
+        m = mr_plan(L, R, 2 * 20480, 256, EPI_SWIGLU)
+        assert m and m.RT == 2 and m.chunks == 1
 
 
 @pytest.mark.parametrize("N,K,epi,splits,here", [
@@ -118,7 +180,7 @@ def test_operands_off_a_16_byte_boundary(L):
                 assert m is None
             else:
                 assert (m is None) == (a is None)
-                assert m is None or (m.any == 1 and m.RT in (4, 6, 8) and m.CT in ((4, 8, 12) if m.RT == 6 else (2, 4, 6, 8, 10, 12)))
+                assert m is None or (m.any == 1 and (m.RT, m.CT) in ANY_ALIGNMENT_BLOCKS)
 
 
 # ---- trajectory selection ---------------------------------------------------------
@@ -146,7 +208,8 @@ def test_selection_loads_match_the_points(L):
 
 @pytest.mark.parametrize("n,P,w,form", [
     (8, 9, 16, SEL_MULTI_5), (24, 25, 16, SEL_MULTI_17), (32, 13, 16, SEL_MULTI_8), (32, 40, 16, SEL_GENERAL),
-    (65, 5, 16, SEL_GENERAL), (16, 65, 16, SEL_GENERAL), (16, 9, 1 << 24, SEL_GENERAL), (16, 9, 1 << 21, SEL_GENERAL)])
+    (65, 5, 16, SEL_GENERAL), (16, 65, 16, SEL_GENERAL), (16, 9, 1 << 24, SEL_GENERAL),
+    (16, 9, 1 << 21, SEL_GENERAL)])
 def test_selection_general_forms(L, n, P, w, form):
     assert select_form(L, n, P, w) == form
 
