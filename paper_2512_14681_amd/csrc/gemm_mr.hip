@@ -184,9 +184,10 @@ static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus, int e
 // -> 22.2, O 25.4 -> 21.1).  33 to 64 rows (two chunks): matrices of 16M
 // elements or more (64 rows: gate/up 97 -> 52, QKV 23.7 -> 19.8; smaller
 // ones lose: O 16.3 -> 18.2), of 26M where its two chunks make one full round
-// of 7 or 8 waves a unit (at 48 rows: 4096 x 4096 / 5504 / 6912 / 7552 16.4 /
-// 20.0 / 23.3 / 25.4 -> 20.3 / 21.9 / 23.8 / 24.4, while 4352 x 4096, a round and
-// a bit, 28.8 -> 19.5), and long K of any size (a down projection of 8192 x 512 / 1024 /
+// of 7 or 8 waves a unit that share K (at 48 rows: 4096 x 4096 / 5504 / 6912 /
+// 7552 16.4 / 20.0 / 23.3 / 25.4 -> 20.3 / 21.9 / 23.8 / 24.4; but 4352 x 4096, a
+// round and a bit, 28.8 -> 19.5, and wide matrices, 32000 x 512 and 16384 x 1024
+// in a step, 20.5 -> 13.6 and 18.1 -> 15.0), and long K of any size (a down projection of 8192 x 512 / 1024 /
 // 1536 at 64 rows 19.0 / 20.6 / 21.6 -> 12.4 / 14.6 / 17.5).  17 to 32 rows
 // (its two-row-tile blocks): long K, and matrices that give every compute unit
 // 8 column tiles (32 rows: gate/up 60.6 -> 47.7, down 36.4 -> 32.9, LM head 218
@@ -226,7 +227,7 @@ static bool mr_takes(int R, int N, int K, int epi_kind, int cus, bool split) {
     GemmShape g{R, N, K, 1, 1, 1};
     gemm_plan(g, epi_kind);
     const long waves = (long)gemm_blocks(g) * g.S * g.C * g.WK;
-    const bool full = waves >= 7 * cus && waves <= 8 * cus;
+    const bool full = T <= 2 * cus && waves >= 7 * cus && waves <= 8 * cus;
     if (full && !split && T < 3 * cus) return false;
     return (long)N * K >= (full ? 26000000 : 16000000);
   }

@@ -120,10 +120,12 @@ def test_long_k_stays_on_the_many_row_kernel(L):
     (3584, 3584, EPI_RESID, False), (8192, 2048, EPI_ARGMAX, False), (8192, 3584, EPI_ARGMAX, True),
     (8208, 2048, EPI_ARGMAX, True), (4608, 3584, EPI_QKV, True), (4352, 4096, EPI_QKV, True),
     (6144, 4096, EPI_QKV, True),
-    (16384, 2048, EPI_SWIGLU, True), (37888, 3584, EPI_SWIGLU, True)])
+    (16384, 2048, EPI_SWIGLU, True), (37888, 3584, EPI_SWIGLU, True),
+    (16384, 1024, EPI_SWIGLU, True), (32000, 512, EPI_ARGMAX, True)])
 def test_33_to_64_rows_by_what_the_streaming_kernel_fills(L, N, K, epi, here):
-    """Matrices whose two row chunks make one full round of the
-    weight-streaming kernel's workgroups stay on it up to 26M elements."""
+    """Matrices of at most two column tiles a unit whose two row chunks make one
+    full round of the weight-streaming kernel's waves stay on it up to 26M
+    elements."""
     for R in (33, 48, 64):
         assert (mr_plan(L, R, N, K, epi) is not None) == here
 
