@@ -474,14 +474,11 @@ static jf_status forward(jf_model* m, const int32_t* d_tokens, int R, const SegA
     attn_block_plan(sa);
     fused = sa.G * sa.qtiles <= kAttnBlockMaxGT && sa.splits <= kAttnMaxSplits && sa.kc_o <= 32;
   }
-  // The layers' projections are planned once: the plan depends on the shapes
-  // and on the operands' alignment, the same in every layer (a plan of the
-  // many-row kernel takes about as long to find as a launch to enqueue).
-  char* l0 = m->layer(0);
-  const GemmRun g_qkv = plan_gemm(dt, R, L.qkv_rows, d, EPI_QKV, xn, pl_d, l0 + L.l_qkv);
-  const GemmRun g_o = plan_gemm(dt, R, d, Hhd, EPI_RESID, m->ws + L.w_attn, pl_h, l0 + L.l_o);
-  const GemmRun g_gu = plan_gemm(dt, R, 2 * F, d, EPI_SWIGLU, xn, pl_d, l0 + L.l_gu);
-  const GemmRun g_down = plan_gemm(dt, R, d, F, EPI_RESID, m->ws + L.w_act, pl_f, l0 + L.l_down);
+  // The layers' projections are planned once, at their first launch, while
+  // the device runs the one before: the plan depends on the shapes and on the
+  // operands' alignment, the same in every layer (a plan of the many-row
+  // kernel takes about as long to find as a launch to enqueue).
+  GemmRun g_qkv{}, g_o{}, g_gu{}, g_down{};
   for (int l = 0; l < c.n_layers; ++l) {
     char* lp = m->layer(l);
     if (fused) {
@@ -511,6 +508,7 @@ static jf_status forward(jf_model* m, const int32_t* d_tokens, int R, const SegA
       ep.page_table = m->at<int32_t>(L.w_pt);
       ep.pos = pos; ep.state = state; ep.rope_cos = m->at<float>(L.w_cos); ep.rope_sin = m->at<float>(L.w_sin);
       ep.H = H; ep.G = G; ep.hd = hd; ep.max_ctx = c.max_ctx; ep.flags = m->flags();
+      if (l == 0) g_qkv = plan_gemm(dt, R, L.qkv_rows, d, EPI_QKV, xn, pl_d, lp + L.l_qkv);
       PROF(JF_KERNEL_QKV);
       HIP_TRY(run_gemm(g_qkv, dt, xn, pl_d, lp + L.l_qkv, ep, st));
       PROF(JF_KERNEL_QKV);
@@ -534,6 +532,7 @@ static jf_status forward(jf_model* m, const int32_t* d_tokens, int R, const SegA
       Epi ep = m->epi();
       ep.kind = EPI_RESID; ep.R = R; ep.f32 = h; ep.ldf = d;
       norm_out(ep, (const float*)(lp + L.l_fn), ss_f, ss_a);
+      if (l == 0) g_o = plan_gemm(dt, R, d, Hhd, EPI_RESID, m->ws + L.w_attn, pl_h, lp + L.l_o);
       PROF(JF_KERNEL_O);
       HIP_TRY(run_gemm(g_o, dt, m->ws + L.w_attn, pl_h, lp + L.l_o, ep, st));
       PROF(JF_KERNEL_O);
@@ -543,6 +542,7 @@ static jf_status forward(jf_model* m, const int32_t* d_tokens, int R, const SegA
       Epi ep = m->epi();
       ep.kind = EPI_SWIGLU; ep.R = R; ep.act = m->ws + L.w_act; ep.act_k = F; ep.act_plane = pl_f;
       norm_in(ep, ss_f);
+      if (l == 0) g_gu = plan_gemm(dt, R, 2 * F, d, EPI_SWIGLU, xn, pl_d, lp + L.l_gu);
       PROF(JF_KERNEL_GATEUP);
       HIP_TRY(run_gemm(g_gu, dt, xn, pl_d, lp + L.l_gu, ep, st));
       PROF(JF_KERNEL_GATEUP);
@@ -556,6 +556,7 @@ static jf_status forward(jf_model* m, const int32_t* d_tokens, int R, const SegA
         norm_out(ep, (const float*)(m->layer(l + 1) + L.l_an), ss_a, ss_f);
       else if (lm != 0)
         norm_out(ep, (const float*)(m->packed + L.p_final), ss_a, ss_f);
+      if (l == 0) g_down = plan_gemm(dt, R, d, F, EPI_RESID, m->ws + L.w_act, pl_f, lp + L.l_down);
       PROF(JF_KERNEL_DOWN);
       HIP_TRY(run_gemm(g_down, dt, m->ws + L.w_act, pl_f, lp + L.l_down, ep, st));
       PROF(JF_KERNEL_DOWN);
