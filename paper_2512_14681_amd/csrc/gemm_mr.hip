@@ -192,11 +192,12 @@ static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus, int e
 // (its two-row-tile blocks): long K, and matrices that give every compute unit
 // 8 column tiles (32 rows: gate/up 60.6 -> 47.7, down 36.4 -> 32.9, LM head 218
 // -> 211, but QKV 16.2 -> 18.1); up to 24 rows, where its blocks still load
-// each weight once, long K only of matrices that give most units less than a
-// column tile (N x 8192 at 17 rows: 1024 / 2048 / 3072 16.6 / 17.2 / 18.3 ->
-// 12.9 / 15.9 / 18.3, 3840 / 4096 19.7 / 19.7 -> 20.8 / 21.7), and of the others
-// only what one round of workgroups holds (24 rows: gate/up 56.0 -> 47.5, LM
-// head 198 -> 210).  10 to 16 rows: of those, the ones whose 64-column groups do
+// each weight once, long K (N x 8192 at 17 rows: 1024 / 2048 / 3072 16.6 / 17.2 /
+// 18.3 -> 12.9 / 15.9 / 18.3; a layer with a down projection of 3328 x 13312 /
+// 3584 x 14336 / 18944 / 4096 x 16384 111.0 / 119.2 / 130.1 / 131.2 -> 107.6 / 115.4 /
+// 129.2 / 130.3, of 3840 / 4096 x 8192 even), and of the others only what one
+// round of workgroups holds (24 rows: gate/up 56.0 -> 47.5, LM head 198 ->
+// 210).  10 to 16 rows: of those, the ones whose 64-column groups do
 // not make full rounds there (gate/up at 10 / 16 rows in a step 47.5 -> 46.4 /
 // 48.0 -> 46.1, at 8 rows 45.8 -> 46.2; 40960 x 512 / 2048, two and a half rounds,
 // at 10 rows 14.0 / 31.9 -> 12.4 / 30.4, but 49152 x 1024 and 32768 x 3072, three
@@ -220,7 +221,7 @@ static bool mr_takes(int R, int N, int K, int epi_kind, int cus, bool split) {
   if (R <= 16)
     return one_round &&
            (T % (4 * cus) != 0 || (split && epi_kind == EPI_ARGMAX) || (long)N * K >= 200000000);
-  if (R <= 24) return one_round || (long_k && 4 * T <= 3 * cus);
+  if (R <= 24) return one_round || long_k;
   if (R <= 32) return long_k || T >= 8 * cus;
   if (R <= 64) {
     if (long_k) return true;
