@@ -114,18 +114,21 @@ __device__ __forceinline__ uint32_t low_bits8(int n) {
 // QT query tiles per block (QT = 1, or 2 for many query tiles over long
 // prefixes, see attn_plan): each key chunk's K and V^T fragments, loaded
 // once, serve all QT tiles of the wave, so the keys are read once per QT
-// tiles.  With QT = 2 one chunk is in
-// flight per wave instead of two (the register budget of two blocks per
-// CU), and the waves' states merge tile after tile.
-// kPermute (column_max): with the permutes the loads of a chunk are held in
-// fewer registers (fp32 at head_dim 128: 126 against 140, where the K and V
-// fragments alone take 128), which waits for memory more often but fits a
-// fourth block on a compute unit.  So the exchange through LDS everywhere
-// (16 heads of 64, 512 rows after 8000 keys, bf16: 92.2 -> 79.3 us with it)
-// except for fp32 at head_dim 128 where the fourth block saves a round of
-// blocks (28 / 4 heads, permutes / exchange: 1 row after 1024 keys 17.8 /
-// 15.4 us, 320 rows alone 48.6 / 42.2; 16 rows after 8000 keys, 896 blocks,
-// 46.1 / 51.5, 192 rows after 500 42.2 / 48.6).
+// tiles.  With QT = 2 one chunk is in flight per wave instead of two (the
+// register budget of two blocks per CU), and the waves' states merge tile
+// after tile.
+// kPermute (column_max): the permutes are the shorter chain (bf16, 64 / 8 heads
+// of 128, 1 row after 1024 keys 11.5 us with the exchange through LDS, 10.8
+// with them; fp32, 16 / 2 heads of 64, 16 rows after 500 11.5 / 11.1), but the
+// compiler may hold the loads of a chunk in fewer registers with them, and
+// wait for memory more often.  It does with two tiles (bf16, 16 heads of 64,
+// 512 rows after 8000 keys: permutes / exchange 92.2 / 79.3 us), which keep
+// the exchange, and for fp32 at head_dim 128 (126 against 140, where the K and
+// V fragments alone take 128), which keeps it except where the fourth block
+// that 126 registers leave room for on a compute unit saves a round of blocks
+// (28 / 4 heads: 1 row after 1024 keys 17.8 / 15.4 us, 320 rows alone 48.6 /
+// 42.2; 16 rows after 8000 keys, 896 blocks, 46.1 / 51.5, 192 rows after 500
+// 42.2 / 48.6).
 template <typename T, int HD, int QT, bool kPermute>
 __global__ void __launch_bounds__(256, 2) k_attn(AttnArgs a) {
   constexpr int NW = 4;  // waves per block
@@ -740,10 +743,10 @@ static hipError_t launch_attn_t(const AttnArgs& a, hipStream_t st) {
   if (kTwo && a.qt == 2) {
     if constexpr (kTwo)
       hipLaunchKernelGGL((k_attn<T, HD, 2, false>), dim3(a.G, (ntiles + 1) / 2, a.splits), dim3(256), 0, st, a);
-  } else if (kBoth && (blocks + 4 * kAttnCus - 1) / (4 * kAttnCus) < (blocks + 3 * kAttnCus - 1) / (3 * kAttnCus)) {
-    if constexpr (kBoth) hipLaunchKernelGGL((k_attn<T, HD, 1, true>), dim3(a.G, ntiles, a.splits), dim3(256), 0, st, a);
+  } else if (kBoth && (blocks + 4 * kAttnCus - 1) / (4 * kAttnCus) == (blocks + 3 * kAttnCus - 1) / (3 * kAttnCus)) {
+    if constexpr (kBoth) hipLaunchKernelGGL((k_attn<T, HD, 1, false>), dim3(a.G, ntiles, a.splits), dim3(256), 0, st, a);
   } else {
-    hipLaunchKernelGGL((k_attn<T, HD, 1, false>), dim3(a.G, ntiles, a.splits), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_attn<T, HD, 1, true>), dim3(a.G, ntiles, a.splits), dim3(256), 0, st, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.splits == 1) return e;
