@@ -194,7 +194,7 @@ static double mr_cost(const MrPlan& m, const MrShape& sh, int NT, int cus, int e
 // -> 211, but QKV 16.2 -> 18.1); up to 24 rows, where its blocks still load
 // each weight once, long K (N x 8192 at 17 rows: 1024 / 2048 / 3072 16.6 / 17.2 /
 // 18.3 -> 12.9 / 15.9 / 18.3; a layer with a down projection of 3328 x 13312 /
-// 3584 x 14336 / 18944 / 4096 x 16384 111.0 / 119.2 / 130.1 / 131.2 -> 107.6 / 115.4 /
+// 3584 x 14336 / 18944 / 4096 x 16384 107.7 / 119.2 / 130.1 / 131.2 -> 104.4 / 115.4 /
 // 129.2 / 130.3, of 3840 / 4096 x 8192 even), and of the others only what one
 // round of workgroups holds (24 rows: gate/up 56.0 -> 47.5, LM head 198 ->
 // 210).  10 to 16 rows: of those, the ones whose 64-column groups do

@@ -12,7 +12,8 @@
 // their fixed points y* loaded at once through range-checked buffer loads
 // (when n <= 64 a load covers floor(64 / n) points: 4 points of a 16-token
 // block per coalesced 256-byte load); lane j then owns point j (so
-// max_points <= 64 there).
+// max_points <= 64 there).  k_traj_select_wide does the same for n = 16 and
+// 32 without counts, four tokens a lane (traj_select_form).
 // k_traj_select (one block per wave, any n and length) is the general path.
 // The unconverged count of a point is a popcount of the wave's mismatch
 // ballot; the choice is exact integer arithmetic, |u w - t_num n| minimal
