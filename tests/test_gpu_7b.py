@@ -115,10 +115,10 @@ def prompt1024():
 @pytest.mark.parametrize("n", [16, 24, 64])
 def test_7b_step_window_logits(env, prompt1024, n):
     """The benchmark's step (n = 16: gate/up on the many-row GEMM, the rest on
-    the weight-streaming kernel), n = 24 (the same split, the weight-streaming
-    kernel with two-row-tile blocks) and n = 64 (all but O on the many-row
-    GEMM, O as two 32-row chunks of the weight-streaming kernel): every row's
-    logits and argmax."""
+    the weight-streaming kernel), n = 24 (down too on the many-row GEMM, the
+    weight-streaming kernel with two-row-tile blocks) and n = 64 (all but O on
+    the many-row GEMM, O as two 32-row chunks of the weight-streaming kernel):
+    every row's logits and argmax."""
     import torch
     dec, model = env["dec"], env["model"]
     dec.reset()
